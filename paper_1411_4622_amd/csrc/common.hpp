@@ -119,68 +119,4 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane)
     return x - v;
 }
 
-// ---------------------------------------------------------------------------
-// device: intersection length of one ray with one pixel (closed form)
-//
-// The chord of the line  x c + y s = s_k  through a unit square, as a
-// function of the signed offset t between the line and the square's centre,
-// is a trapezoid: constant 1 / max(|c|,|s|) for |t| <= (hi - lo)/2, falling
-// linearly to 0 at |t| = (hi + lo)/2, with hi/lo = max/min(|c|, |s|).
-// Near-axis rays make the ramp steep (slope 1 / (hi lo)), so t is formed
-// with error-free products and sums (FMA-based) to keep the length error
-// near 1e-14 even on 1024-pixel grids.
-// Axis-parallel rays (c or s exactly 0) go to the pixel whose half-open
-// interval [left, left + 1) or [bottom, bottom + 1) contains them.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double sum_err(double a, double b, double s)
-{
-    const double bb = s - a;
-    return (a - (s - bb)) + (b - bb);
-}
-
-// t = sk - (xc c + yc s) as an unevaluated sum hi + *lo (error-free
-// products and sums: the pair is exact to about 1e-32)
-__device__ __forceinline__ double ray_offset(double sk, double xc, double yc, double c, double s,
-                                             double* lo)
-{
-    const double p = xc * c, ep = fma(xc, c, -p);
-    const double q = yc * s, eq = fma(yc, s, -q);
-    const double a = sk - p, ea = sum_err(sk, -p, a);
-    const double b = a - q, eb = sum_err(a, -q, b);
-    *lo = (ea + eb) - (ep + eq);
-    return b;
-}
-
-__device__ __forceinline__ double pixel_ray_length(double xl, double yb, double c, double s,
-                                                   double sk)
-{
-    if (s == 0.0) {
-        const double x = sk * c;
-        return (x >= xl && x < xl + 1.0) ? 1.0 : 0.0;
-    }
-    if (c == 0.0) {
-        const double y = sk * s;
-        return (y >= yb && y < yb + 1.0) ? 1.0 : 0.0;
-    }
-    double th_lo;
-    const double th = ray_offset(sk, xl + 0.5, yb + 0.5, c, s, &th_lo);
-    const double t = fabs(th + th_lo);
-    const double a = fabs(c), b = fabs(s);
-    const double hi = fmax(a, b), lo = fmin(a, b);
-    const double flat = 0.5 * (hi - lo), edge = 0.5 * (hi + lo);
-    double l = 0.0;
-    if (t <= flat) {
-        l = 1.0 / hi;
-    } else if (t < edge) {
-        // 2 (edge - |t|) = (E - 2|th|) + (E_err - 2 sgn th_lo) with E = hi + lo
-        // split error-free; on the ramp the first difference is exact
-        // (Sterbenz) whenever the slope 1 / (hi lo) is large
-        const double sg = th < 0.0 ? -1.0 : 1.0;
-        const double E = hi + lo, Ee = sum_err(hi, lo, E);
-        const double u = 0.5 * ((E - 2.0 * sg * th) + (Ee - 2.0 * sg * th_lo));
-        l = u / (hi * lo);
-    }
-    return l > kTau ? l : 0.0;
-}
-
 }  // namespace pila
