@@ -98,8 +98,6 @@ struct ChainShared {
     int32_t p[kMaxCand];
     double red[kMaxWaves];
     double scalar[4];
-    double fnstar;
-    int32_t pstar;
     int32_t ticket;
     int32_t stop;
 };
@@ -181,18 +179,7 @@ __device__ __forceinline__ double dpp_mov(double x)
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ float swz16(float x)
-{
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
-}
-__device__ __forceinline__ double swz16(double x)
-{
-    const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(x), 0x401F);
-    const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(x), 0x401F);
-    return __hiloint2double(hi, lo);
-}
-
-// value of lane ^ O (O = 1, 2, 4, 8, 16, 32).  For O = 4 and O = 8 the row
+// value of lane ^ O (O = 1, 2, 4, 8).  For O = 4 and O = 8 the row
 // mirrors are used, which equal the xor partner once every quad (O = 4) or
 // half-row (O = 8) holds one value, as it does inside a butterfly.
 template <int O, typename T>
@@ -201,9 +188,63 @@ __device__ __forceinline__ T xor_partner(T x)
     if constexpr (O == 1) return dpp_mov<0xB1>(x);
     else if constexpr (O == 2) return dpp_mov<0x4E>(x);
     else if constexpr (O == 4) return dpp_mov<0x141>(x);
-    else if constexpr (O == 8) return dpp_mov<0x140>(x);
-    else if constexpr (O == 16) return swz16(x);
-    else return __shfl_xor(x, 32, kWave);
+    else return dpp_mov<0x140>(x);
+}
+
+// x + value of lane ^ O, and the lesser of the two.  For O = 16 and 32 the
+// wavefront's rows (16 lanes) or halves change places between two registers
+// holding x (v_permlane16_swap, v_permlane32_swap), which leaves one partner
+// of each pair in either register: two register operations in place of a
+// round trip through the LDS crossbar.  The operands' order may differ from
+// x + partner; the sum does not.
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <int O>
+__device__ __forceinline__ u32x2 swap_rows(uint32_t x)
+{
+    if constexpr (O == 16)
+        return __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    else
+        return __builtin_amdgcn_permlane32_swap(x, x, false, false);
+}
+template <int O>
+__device__ __forceinline__ void swap_pair(float x, float* a, float* b)
+{
+    const u32x2 r = swap_rows<O>(__float_as_uint(x));
+    *a = __uint_as_float(r.x);
+    *b = __uint_as_float(r.y);
+}
+template <int O>
+__device__ __forceinline__ void swap_pair(double x, double* a, double* b)
+{
+    const u32x2 lo = swap_rows<O>((uint32_t)__double2loint(x)), hi = swap_rows<O>((uint32_t)__double2hiint(x));
+    *a = __hiloint2double((int)hi.x, (int)lo.x);
+    *b = __hiloint2double((int)hi.y, (int)lo.y);
+}
+
+template <int O, typename T>
+__device__ __forceinline__ T xor_add(T x)
+{
+    if constexpr (O == 16 || O == 32) {
+        T a, b;
+        swap_pair<O>(x, &a, &b);
+        return a + b;
+    } else {
+        return x + xor_partner<O>(x);
+    }
+}
+
+template <int O>
+__device__ __forceinline__ double xor_min(double x)
+{
+    double a, b;
+    if constexpr (O == 16 || O == 32) {
+        swap_pair<O>(x, &a, &b);
+    } else {
+        a = x;
+        b = xor_partner<O>(x);
+    }
+    return b < a ? b : a;
 }
 
 template <int O, int LPC, int K, typename T>
@@ -211,7 +252,7 @@ __device__ __forceinline__ void butterfly_level(T (&a)[K])
 {
     if constexpr (O < LPC) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) a[k] = a[k] + xor_partner<O>(a[k]);
+        for (int k = 0; k < K; ++k) a[k] = xor_add<O>(a[k]);
     } else {
         constexpr int st = O / LPC;
 #pragma unroll
@@ -247,15 +288,15 @@ __device__ __forceinline__ T wave_canon_sum(T x)
     return canon_sum<64>(a);
 }
 
+// minimum over the wavefront of a value that is not NaN in any lane
 __device__ __forceinline__ double wave_min(double x)
 {
-    x = fmin(x, xor_partner<1>(x));
-    x = fmin(x, xor_partner<2>(x));
-    x = fmin(x, xor_partner<4>(x));
-    x = fmin(x, xor_partner<8>(x));
-    x = fmin(x, xor_partner<16>(x));
-    x = fmin(x, xor_partner<32>(x));
-    return x;
+    x = xor_min<1>(x);
+    x = xor_min<2>(x);
+    x = xor_min<4>(x);
+    x = xor_min<8>(x);
+    x = xor_min<16>(x);
+    return xor_min<32>(x);
 }
 
 __device__ __forceinline__ double readlane_f64(double v, int l)
@@ -263,6 +304,20 @@ __device__ __forceinline__ double readlane_f64(double v, int l)
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
     return __hiloint2double(hi, lo);
+}
+// A uniform value kept in a vector register (the step loops run out of scalar
+// ones first, and a spilled scalar costs two vector operations)
+template <typename T>
+__device__ __forceinline__ T in_vector(T x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ int64_t readlane_i64(int64_t v, int l)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 __device__ __forceinline__ double uniform_f64(double v)
 {
@@ -317,18 +372,27 @@ __device__ __forceinline__ uint32_t ridx(const ChainJob& J, int32_t g)
 // ---------------------------------------------------------------------------
 struct Schedule {
     int64_t stage, next;  // current stage, first step of the following stage
+    // (stage + 1) n_steps = n_stages whole + rest; per stage they grow by the
+    // quotient and remainder of n_steps / n_stages, so that no step divides
+    int64_t whole, quot;
+    int32_t rest, rem, n_stages;
     double T0, TN, dT, NN;
     int kind;
     double T, invT;  // temperature of the current stage and its reciprocal
-    __device__ void start(int64_t s, int64_t n_steps, int32_t n_stages, double t0, double tn, int k)
+    __device__ void start(int64_t s, int64_t n_steps, int32_t stages, double t0, double tn, int k)
     {
         T0 = t0;
         TN = tn;
         kind = k;
+        n_stages = stages;
         NN = (double)n_stages;
         dT = (t0 - tn) / NN;
         stage = n_steps > 0 ? (s * (int64_t)n_stages) / n_steps : 0;
-        next = first_of(stage + 1, n_steps, n_stages);
+        quot = n_steps / n_stages;
+        rem = (int32_t)(n_steps - quot * n_stages);
+        whole = ((stage + 1) * n_steps) / n_stages;
+        rest = (int32_t)((stage + 1) * n_steps - whole * n_stages);
+        next = whole + (rest > 0 ? 1 : 0);
         set();
     }
     __device__ void set()
@@ -342,16 +406,18 @@ struct Schedule {
             T = T0 - x * dT;
         invT = 1.0 / T;
     }
-    __device__ static int64_t first_of(int64_t k, int64_t n_steps, int32_t n_stages)
-    {
-        return (k * n_steps + n_stages - 1) / n_stages;
-    }
-    __device__ double at(int64_t s, int64_t n_steps, int32_t n_stages)
+    __device__ double at(int64_t s)
     {
         if (s >= next) {
             while (s >= next) {
                 ++stage;
-                next = first_of(stage + 1, n_steps, n_stages);
+                whole += quot;
+                rest += rem;
+                if (rest >= n_stages) {
+                    rest -= n_stages;
+                    ++whole;
+                }
+                next = whole + (rest > 0 ? 1 : 0);
             }
             set();
         }
@@ -460,10 +526,10 @@ __device__ void rebuild_tile(const ChainJob& J, Real* __restrict__ r, int G, int
                     if (q0 + 16 * c < e) acc = fma((double)lc[c], fv[c], acc);
             }
         }
-        acc = acc + xor_partner<1>(acc);
-        acc = acc + xor_partner<2>(acc);
-        acc = acc + xor_partner<4>(acc);
-        acc = acc + xor_partner<8>(acc);
+        acc = xor_add<1>(acc);
+        acc = xor_add<2>(acc);
+        acc = xor_add<4>(acc);
+        acc = xor_add<8>(acc);
         if (ql == i) mine = acc;
     }
     const int g = t * kWave + lane;
@@ -660,49 +726,111 @@ __device__ inline void write_stats(const ChainJob& J, const ChainState& cs)
 
 struct Decision {
     int ms;
-    double S, dC;
+    double S;
     bool accept;
 };
 
-// BoME (first minimal S; a NaN never wins) and Step 4's acceptance.  Every
-// wavefront computes the same answer; each lane forms the cost change of its
-// own estimate so the cost arithmetic overlaps the minimum search.  The test
-// N1 < exp(-dC / T) is settled by comparing -dC / T with ln N1 (computed
-// ahead of time) whenever they differ by more than 1e-12 relative, far
-// beyond the rounding of exp, the division and the logarithm; inside that
-// band (and for N1 = 0) it is evaluated exactly as written.
-__device__ __forceinline__ Decision decide(const double* S, int M, int lane, double sse, double co,
-                                           double KU, double T, double invT, double N1, double lnN1)
+// Delta C of Eq. 7 for a change S of the squared-residual sum sse
+__device__ __forceinline__ double cost_change(double S, double sse, double KU)
 {
-    double v = lane < M ? S[lane] : INFINITY;
-    if (v != v) v = INFINITY;
-    const double cn = sqrt(fmax(sse + v, 0.0) / KU);
+    const double cn = sqrt(fmax(sse + S, 0.0) / KU), co = sqrt(sse / KU);
     const double den = cn + co;
-    const double dC = den == 0.0 ? 0.0 : (v / KU) / den;
-    const double vmin = wave_min(v);
+    return den == 0.0 ? 0.0 : (S / KU) / den;
+}
+
+// Step 4 as written.  The test N1 < exp(-dC / T) is settled by comparing
+// -dC / T with ln N1 (computed ahead of time) whenever they differ by more
+// than 1e-12 relative, far beyond the rounding of exp, the division and the
+// logarithm; inside that band (and for N1 = 0) it is evaluated exactly.
+__device__ __forceinline__ bool accepts(double dC, double T, double invT, double N1, double lnN1)
+{
+    if (dC <= 0.0) return true;
+    const double x = -dC * invT;
+    const double margin = 1e-12 * (fabs(lnN1) + fabs(x));
+    if (N1 > 0.0 && x < lnN1 - margin) return false;
+    if (N1 > 0.0 && x > lnN1 + margin) return true;
+    return N1 < exp(-dC / T);
+}
+
+// BoME (first minimal S; a NaN never wins) and Step 4's acceptance.  S: each
+// lane's own estimate's sum (lanes M and above: anything).  Every wavefront
+// computes the same answer, and the whole workgroup waits for it, so only
+// what the answer needs is formed: a change that does not raise the sum is
+// accepted by its sign; one that does is first estimated in FP32 (one
+// hardware square root per term and a reciprocal, relative error below 1e-6
+// over the checked range) and settled by it when -dC / T and ln N1 differ by
+// more than 4e-6 relative; the FP64 square roots and divisions of Eq. 7 run
+// only inside that band.  (With both square roots and three divisions formed
+// for every lane the decision took 1200 clocks of a step, now 640: 64 x 64,
+// 90 angles, M = 4, FP64.)
+__device__ __forceinline__ Decision decide(double S, int M, int lane, double sse, double KU, double invKU,
+                                           double T, double invT, double N1, double lnN1)
+{
+    const double v = lane < M && S == S ? S : INFINITY;
+    double vmin = xor_min<8>(xor_min<4>(xor_min<2>(xor_min<1>(v))));
+    if (M > 16)
+        vmin = xor_min<32>(xor_min<16>(vmin));
+    else
+        vmin = readlane_f64(vmin, 0);  // every estimate is in the first 16 lanes
     const unsigned long long mask = __ballot(v == vmin);
     Decision dn;
-    dn.ms = mask ? uniform_i32(__ffsll((long long)mask) - 1) : 0;
+    dn.ms = uniform_i32(__ffsll((long long)mask) - 1);
     dn.S = readlane_f64(v, dn.ms);
-    dn.dC = readlane_f64(dC, dn.ms);
-    if (dn.dC <= 0.0) {
+    const bool finite = sse >= 0.0 && sse < INFINITY;
+    if (finite && dn.S <= 0.0) {
         dn.accept = true;
-    } else {
-        const double x = -dn.dC * invT;
-        const double margin = 1e-12 * (fabs(lnN1) + fabs(x));
-        if (N1 > 0.0 && x < lnN1 - margin)
-            dn.accept = false;
-        else if (N1 > 0.0 && x > lnN1 + margin)
-            dn.accept = true;
-        else
-            dn.accept = N1 < exp(-dn.dC / T);
+        return dn;
     }
+    if (finite) {
+        const float n = (float)(dn.S * invKU), b = (float)(sse * invKU), a = (float)((sse + dn.S) * invKU);
+        if (n > 1e-30f && a < 1e30f) {
+            const float den = __builtin_amdgcn_sqrtf(a) + __builtin_amdgcn_sqrtf(b);
+            const float x = -n * __builtin_amdgcn_rcpf(den) * (float)invT, y = (float)lnN1;
+            const float margin = 4e-6f * (fabsf(x) + fabsf(y));
+            if (x < y - margin) {
+                dn.accept = false;
+                return dn;
+            }
+            if (x > y + margin) {
+                dn.accept = true;
+                return dn;
+            }
+        }
+    }
+    dn.accept = accepts(cost_change(dn.S, sse, KU), T, invT, N1, lnN1);
     return dn;
 }
 
-// bookkeeping and trace after a decision; d_star is the winner's change
-__device__ __forceinline__ void count_decision(const ChainJob& J, ChainState& cs, const Decision& dn,
-                                               double d_star, int64_t s)
+// The trace of up to 64 steps, one a lane, until it is stored: a step then
+// costs a few register moves, and Delta C is formed for 64 steps at once.
+struct Trace {
+    double S, sse;
+    int32_t m;       // chosen estimate, -1 - it when rejected
+    int64_t first;   // first step held (those up to the next multiple of 64 follow)
+    __device__ __forceinline__ void store(const ChainJob& J, int64_t end, int lane, double KU)
+    {
+        const int64_t s = (first & ~(int64_t)(kWave - 1)) + lane;
+        if (s >= first && s < end) {
+            const bool acc = m >= 0;
+            if (J.tr_m) J.tr_m[s] = acc ? m : -1 - m;
+            if (J.tr_acc) J.tr_acc[s] = acc ? 1 : 0;
+            if (J.tr_dc) J.tr_dc[s] = cost_change(S, sse, KU);
+        }
+        first = end;
+    }
+    __device__ __forceinline__ void add(const ChainJob& J, const Decision& dn, double sse_before, int64_t s, int lane,
+                                        double KU)
+    {
+        const bool here = lane == (int)(s & (kWave - 1));
+        S = here ? dn.S : S;
+        sse = here ? sse_before : sse;
+        m = here ? (dn.accept ? dn.ms : -1 - dn.ms) : m;
+        if ((s & (kWave - 1)) == kWave - 1) store(J, s + 1, lane, KU);
+    }
+};
+
+// bookkeeping after a decision; d_star is the winner's change
+__device__ __forceinline__ void count_decision(ChainState& cs, const Decision& dn, double d_star)
 {
     if (dn.accept) {
         cs.sse += dn.S;
@@ -711,11 +839,6 @@ __device__ __forceinline__ void count_decision(const ChainJob& J, ChainState& cs
             ++cs.accepts_nz;
             ++cs.since;
         }
-    }
-    if (threadIdx.x == 0) {
-        if (J.tr_m) J.tr_m[s] = dn.ms;
-        if (J.tr_acc) J.tr_acc[s] = dn.accept ? 1 : 0;
-        if (J.tr_dc) J.tr_dc[s] = dn.dC;
     }
 }
 
@@ -742,6 +865,7 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
     const double KU = (double)J.K * (double)J.U;
     const int M = J.m_cand;
+    const double invKU = 1.0 / KU;
     Real* r = LDS ? (Real*)lds : (Real*)J.r;
     // segmented (global residual only): the chain state comes from the carry
     // and the chain returns when a resync is due, which then runs grid-wide
@@ -801,8 +925,13 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
         return fn - fo;
     };
 
+    Trace trace{0.0, 0.0, 0, cs.s_begin};
+    const bool traced = wave == 0 && (J.tr_m || J.tr_acc || J.tr_dc);
+    auto trace_end = [&](int64_t end) {  // before the chain, or its segment, ends
+        if (traced && trace.first < end) trace.store(J, end, lane, KU);
+    };
     for (int64_t s = cs.s_begin; s < cs.n_steps; ++s) {
-        const double T = sched.at(s, cs.n_steps, J.n_stages);
+        const double T = sched.at(s);
         // next step's support lookups, in flight during this step
         int32_t np[KA];
         double ndel[KA];
@@ -900,13 +1029,13 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
                 de[k] = J.row_ptr[np[k] + 1];
             }
         }
-        const double co = sqrt(cs.sse / KU);
         const double N1 = unit53(philox4x64(J.seed, J.chain_id, (uint64_t)s, 0, 1, 0).w0);
-        const double lnN1 = log(N1), invT = 1.0 / T;
+        const double lnN1 = log(N1), invT = sched.invT;
         cancel_probe(J, sh, s);
         __syncthreads();
-        const Decision dn = decide(sh.S, M, lane, cs.sse, co, KU, T, invT, N1, lnN1);
-        const double d_star = uniform_f64(sh.d[dn.ms]);
+        const double dv = sh.d[lane];  // with the sums, so that no second LDS trip follows the decision
+        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
+        const double d_star = readlane_f64(dv, dn.ms);
         // Eq. 6 for the winner, by the whole workgroup (one entry per thread;
         // the row's rays are distinct, so no two threads touch one value); an
         // accepted zero change leaves image and residual as they are
@@ -919,10 +1048,12 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
             }
             if (threadIdx.x == 0) J.f[sh.p[dn.ms]] = sh.fn[dn.ms];
         }
-        count_decision(J, cs, dn, d_star, s);
+        if (traced) trace.add(J, dn, cs.sse, s, lane, KU);
+        count_decision(cs, dn, d_star);
         if (f32 && J.resync_every > 0 && cs.since >= J.resync_every) {
             if (!LDS && segmented) {
                 __syncthreads();
+                trace_end(s + 1);
                 save_carry(J, cs, s + 1, true);
                 return;
             }
@@ -936,9 +1067,11 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
         }
     }
     if (segmented) {
+        trace_end(cs.n_steps);
         save_carry(J, cs, cs.n_steps, false);
         return;
     }
+    trace_end(cs.n_steps);
     write_stats(J, cs);
 }
 
@@ -1086,9 +1219,15 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
         const int64_t rb = uniform_i64(sp.rb[cs.s_begin & 1][m1]);
         row_chunk(rb, uniform_i64(sp.re[cs.s_begin & 1][m1]) - rb, pc, pl);
     }
+    const double invKU = 1.0 / KU;
+    Trace trace{0.0, 0.0, 0, cs.s_begin};
+    const bool traced = g == 0 && wave == 0 && (J.tr_m || J.tr_acc || J.tr_dc);
+    auto trace_end = [&](int64_t end) {  // before the chain, or its segment, ends
+        if (traced && trace.first < end) trace.store(J, end, lane, KU);
+    };
     for (int64_t s = cs.s_begin; s < cs.n_steps; ++s) {
         const int pb = (int)(s & 1);
-        const double T = sched.at(s, cs.n_steps, J.n_stages);
+        const double T = sched.at(s);
         const bool more = s + 1 < cs.n_steps;
         // step s + 1's draws; the support lookups are in flight while this
         // step's rows are scored
@@ -1151,9 +1290,8 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
             ne = J.row_ptr[np + 1];
             nfo = J.f[np];
         }
-        const double co = sqrt(cs.sse / KU);
         const double N1 = unit53(philox4x64(J.seed, J.chain_id, (uint64_t)s, 0, 1, 0).w0);
-        const double lnN1 = log(N1), invT = 1.0 / T;
+        const double lnN1 = log(N1), invT = sched.invT;
         if (wave == 0) {
             bool need = lane < M && lane % G != g;
             const uint64_t want = split_stamp(s);
@@ -1182,6 +1320,7 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
         }
         __syncthreads();
         if (sp.fail) {
+            trace_end(s);
             cs.status = PILA_ETIMEDOUT;
             cs.n_steps = 0;
             break;
@@ -1190,12 +1329,16 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
         // applied
         int32_t qc[U];
         Real ql[U];
-        if (m1 < M && more) {
-            const int64_t rb = uniform_i64(sp.rb[pb ^ 1][m1]);
-            row_chunk(rb, uniform_i64(sp.re[pb ^ 1][m1]) - rb, qc, ql);
+        {  // (unconditional: the waits below then count these loads)
+            const bool on = m1 < M && more;
+            const int mm = m1 < M ? m1 : 0;
+            const int64_t rb = uniform_i64(sp.rb[pb ^ 1][mm]);
+            row_chunk(rb, on ? uniform_i64(sp.re[pb ^ 1][mm]) - rb : 0, qc, ql);
         }
-        const Decision dn = decide(sh.S, M, lane, cs.sse, co, KU, T, invT, N1, lnN1);
-        const double d_star = uniform_f64(sp.d[pb][dn.ms]);
+        const double dv = sp.d[pb][lane], fv = sp.fn[pb][lane];
+        const int32_t pv = sp.p[pb][lane];
+        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
+        const double d_star = readlane_f64(dv, dn.ms);
         const bool change = dn.accept && d_star != 0.0;
         int32_t pstar = 0;
         double fnstar = 0.0;
@@ -1222,11 +1365,12 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
                 for (int k = 0; k < kSc; ++k)
                     if (q0 + k * nt < e) r[at[k]] = rv[k] + dr * lv[k];
             }
-            pstar = uniform_i32(sp.p[pb][dn.ms]);
-            fnstar = uniform_f64(sp.fn[pb][dn.ms]);
+            pstar = __builtin_amdgcn_readlane(pv, dn.ms);
+            fnstar = readlane_f64(fv, dn.ms);
             if (threadIdx.x == 0) J.f[pstar] = fnstar;
         }
-        count_decision(J, cs, dn, d_star, s);
+        if (traced) trace.add(J, dn, cs.sse, s, lane, KU);
+        count_decision(cs, dn, d_star);
         // step s + 1's estimates: the image value read before this step's
         // change, patched with it
         if (book && more) {
@@ -1242,11 +1386,13 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
         }
         if (f32 && J.resync_every > 0 && cs.since >= J.resync_every) {
             __syncthreads();
+            trace_end(s + 1);
             if (g == 0) save_carry(J, cs, s + 1, true);
             return;
         }
         __syncthreads();
     }
+    trace_end(cs.n_steps);
     if (g == 0) save_carry(J, cs, cs.n_steps, false);
 }
 
@@ -1317,6 +1463,27 @@ __device__ __forceinline__ int slot_patch(int32_t tk)
     return ((tk >> (kSlotPosBits - 1)) & ~1) | (tk & 1);
 }
 
+// Waits for the wavefront's loads.  Before a step loop: the loop's own waits
+// then count only its own loads, whatever order the compiler gave the ones
+// before it.
+__device__ __forceinline__ void wait_loads()
+{
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+}
+
+// What drawing a block of estimates needs of the chain's descriptor.  Read
+// where it is used from the descriptor in constant memory, when the caller
+// has it there (the address made opaque, so that the fields are not held in
+// scalar registers, which the step loop has too few of).
+struct DrawArgs {
+    uint64_t seed, chain_id;
+    const int32_t* support;
+    const int64_t* row_ptr;
+    double delta_max;
+    int32_t P;
+};
+typedef const __attribute__((address_space(4))) ChainJob* ConstJob;
+
 template <typename Real, int E>
 struct RowSet {
     int32_t col[E];
@@ -1331,7 +1498,7 @@ struct RowSet {
 };
 
 struct Draws {  // one block of steps: lane j <-> (step j / CPW, estimate slot j % CPW)
-    int64_t base;
+    int32_t drawn, block;  // blocks (step / steps per block) whose draws, and whose row offsets, are held
     uint32_t b;
     int32_t p, n;
     double delta, N1, lnN1;
@@ -1369,8 +1536,17 @@ __device__ void lds_residual_store(const ChainJob& J, Real* r, const Real* rl)
 // Either way the same float results.
 template <typename Real, bool RLDS, int CPW, int E, bool SERVED = false, bool TK = false, typename LenT = Real,
           bool LATE = false>
-__device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, bool segmented)
+__device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, bool segmented,
+                                ConstJob constant = nullptr)
 {
+    auto draw_args = [&]() -> DrawArgs {
+        if (constant) {
+            ConstJob p = constant;
+            asm volatile("" : "+s"(p));
+            return {p->seed, p->chain_id, p->support, p->row_ptr, p->delta_max, p->P};
+        }
+        return {J.seed, J.chain_id, J.support, J.row_ptr, J.delta_max, J.P};
+    };
     constexpr int LPC = kWave / CPW;  // lanes per estimate
     constexpr int BL = kWave / CPW;   // steps per block of draws
     constexpr int kLdsFlag = kRaySlotLds;
@@ -1381,6 +1557,7 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     const int M = J.m_cand;
     const int m_mine = wave * CPW + slot;
     const bool active = m_mine < M;
+    const double invKU = 1.0 / KU;
     // RLDS: the whole residual lives in LDS.  Otherwise the residual is in
     // global memory except angles u < UL, which live in LDS (rl); rvB holds
     // the global values one step ahead and the table of the last accepted
@@ -1401,29 +1578,28 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     Schedule sched;
     sched.start(s_begin, n_steps, J.n_stages, cs.T0, cs.TN, J.schedule);
 
+    // The draws of a block of steps, in two stages so that neither waits for
+    // memory: the estimates (and the support lookup issued), later the row
+    // offsets.  Steps past the end draw nothing and have empty rows.
     Draws cur, nxt;
-    auto fill = [&](Draws& D, int64_t base) {
-        D.base = base;
-        const int64_t s = base + lane / CPW;
+    auto draw = [&](Draws& D, int32_t block) {
+        const DrawArgs C = draw_args();
+        const int64_t s = (int64_t)block * BL + lane / CPW;
         const int m = wave * CPW + lane % CPW;
+        D.drawn = block;
         D.p = 0;
-        D.n = 0;
-        D.b = 0;
         D.delta = 0.0;
         D.N1 = 0.0;
         D.lnN1 = 0.0;
         // the key is made opaque here, so that the round keys are formed per
         // block instead of being held in scalar registers across the loop
-        uint64_t k0 = lane0(J.seed), k1 = lane0(J.chain_id);
+        uint64_t k0 = lane0(C.seed), k1 = lane0(C.chain_id);
         asm volatile("" : "+s"(k0), "+s"(k1));
         if (s < n_steps) {
             if (m < M) {
                 const Words4 w = philox4x64(k0, k1, (uint64_t)s, (uint64_t)m, 0, 0);
-                D.p = J.support[__umul64hi(w.w0, (uint64_t)J.P)];
-                D.delta = J.delta_max * (2.0 * unit53(w.w1) - 1.0);
-                const int64_t b0 = J.row_ptr[D.p];
-                D.b = (uint32_t)b0;
-                D.n = (int32_t)(J.row_ptr[D.p + 1] - b0);
+                D.p = C.support[__umul64hi(w.w0, (uint64_t)C.P)];
+                D.delta = C.delta_max * (2.0 * unit53(w.w1) - 1.0);
             }
             if (lane % CPW == 0) {
                 D.N1 = unit53(philox4x64(k0, k1, (uint64_t)s, 0, 1, 0).w0);
@@ -1431,41 +1607,49 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
             }
         }
     };
-    cur.base = nxt.base = -1;
+    auto offsets = [&](Draws& D, int32_t block) {
+        const DrawArgs C = draw_args();
+        D.block = block;
+        const bool on = (int64_t)block * BL + lane / CPW < n_steps && wave * CPW + lane % CPW < M;
+        const int64_t b0 = C.row_ptr[D.p];
+        D.b = (uint32_t)b0;
+        D.n = on ? (int32_t)(C.row_ptr[D.p + 1] - b0) : 0;
+    };
 
+    // the draws to go on from step t
+    auto draws_from = [&](int64_t t) {
+        const int32_t block = (int32_t)(t / BL);
+        draw(cur, block);
+        offsets(cur, block);
+        nxt.drawn = nxt.block = -1;
+    };
+
+    // Row of step t.  Every load is issued unconditionally (past the row, and
+    // for steps past the end, entry 0 is read): the compiler then knows how
+    // many loads are outstanding wherever an earlier one is used, and waits
+    // for that one alone.  With the loads in a branch it counted none of
+    // them, and each step waited for the rows it had just asked for.
     auto prefetch = [&](RowSet<Real, E>& S, int64_t t) {
-        if (t >= n_steps) {
-            S.p = 0;
-            S.n = 0;
-            S.delta = 0.0;
-            S.N1 = 0.0;
-            S.lnN1 = 0.0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                S.col[e] = 0;
-                S.len[e] = (Real)0;
-                S.tk[e] = 0;
-            }
-            return;
+        const int32_t block = uniform_i32((int32_t)(t / BL));
+        if (cur.block != block) cur = nxt;
+        const int j = uniform_i32((int)t & (BL - 1));
+        if (j >= BL / 4 && nxt.drawn != block + 1) draw(nxt, block + 1);  // the next block's, early
+        if (j >= BL / 2 && nxt.block != block + 1) offsets(nxt, block + 1);
+        uint32_t b;
+        if constexpr (CPW == 1) {  // one estimate a wavefront: the draw's lane is the step's
+            S.p = in_vector(__builtin_amdgcn_readlane(cur.p, j));
+            S.n = in_vector(__builtin_amdgcn_readlane(cur.n, j));
+            b = (uint32_t)__builtin_amdgcn_readlane((int)cur.b, j);
+            S.delta = in_vector(readlane_f64(cur.delta, j));
+        } else {
+            const int src = j * CPW + slot;
+            S.p = __shfl(cur.p, src, kWave);
+            S.n = __shfl(cur.n, src, kWave);
+            b = (uint32_t)__shfl((int)cur.b, src, kWave);
+            S.delta = __shfl(cur.delta, src, kWave);
         }
-        const int64_t base = t - t % BL;
-        if (cur.base != base) {
-            if (nxt.base == base)
-                cur = nxt;
-            else
-                fill(cur, base);
-        }
-        const int j = (int)(t - base);
-        if (j == BL / 2 && base + BL < n_steps) fill(nxt, base + BL);  // next block, early
-        const int src = j * CPW + slot;
-        S.p = __shfl(cur.p, src, kWave);
-        S.n = __shfl(cur.n, src, kWave);
-        const uint32_t b = (uint32_t)__shfl((int)cur.b, src, kWave);
-        S.delta = __shfl(cur.delta, src, kWave);
-        S.N1 = __shfl(cur.N1, j * CPW, kWave);
-        S.lnN1 = __shfl(cur.lnN1, j * CPW, kWave);
-        // loads are unconditional (entries past the row read entry 0) so that
-        // nothing waits for them here; validity is tested where they are used
+        S.N1 = in_vector(readlane_f64(cur.N1, j * CPW));
+        S.lnN1 = in_vector(readlane_f64(cur.lnN1, j * CPW));
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int q = li + e * LPC;
@@ -1499,13 +1683,7 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     };
 
     RowSet<Real, E> A, B, C;
-    prefetch(A, s_begin);
-    prefetch(B, s_begin + 1);
     __syncthreads();  // setup (residual, LDS part, temperatures, patch table) complete
-    table_slots(A);
-#pragma unroll
-    for (int e = 0; e < E; ++e) A.rv[e] = in_lds(A.tk[e]) ? rl[A.tk[e] & ~kLdsFlag] : rget(gcol(A, e));
-    A.fo = J.f[A.p];
     bool patch = false;     // apply the table of step s - 1 to X.rv
     int32_t lp = -1;        // last accepted pixel (step s - 1) and its value
     double lfn = 0.0;
@@ -1516,10 +1694,14 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     // Returns true when the chain stops here: a segmented chain for a
     // resync, or a served chain that has been cancelled (then cancelled is set).
     bool cancelled = false;
-    double co = sqrt(cs.sse / KU);  // C of Eq. 4 before the step
+    Trace trace{0.0, 0.0, 0, s_begin};
+    const bool traced = wave == 0 && (J.tr_m || J.tr_acc || J.tr_dc);
+    auto trace_end = [&](int64_t end) {  // before the chain, or its segment, ends
+        if (traced && trace.first < end) trace.store(J, end, lane, KU);
+    };
     auto step = [&](RowSet<Real, E>& X, RowSet<Real, E>& Y, RowSet<Real, E>& Z, int64_t s)
                     __attribute__((always_inline)) -> bool {
-        const double T = sched.at(s, n_steps, J.n_stages);
+        const double T = sched.at(s);
         const double invT = sched.invT;
         // next step's global operands, issued before this step is scored so
         // that they have the whole step to arrive (the residual already holds
@@ -1528,10 +1710,8 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         table_slots(Y);
         if (!RLDS) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                Y.rv[e] = (Real)0;
-                if (!(Y.tk[e] & kLdsFlag)) Y.rv[e] = rget(gcol(Y, e));
-            }
+            for (int e = 0; e < E; ++e)  // (unconditional, as in prefetch: an entry in LDS reads value 0 here)
+                Y.rv[e] = rget(in_lds(Y.tk[e]) ? 0u : gcol(Y, e));
         }
         Y.fo = J.f[Y.p];
         if (!RLDS && patch) {  // the previous step's accepted change
@@ -1563,13 +1743,19 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         if (active && li == 0) {
             sh.S[m_mine] = (double)S;
             sh.d[m_mine] = d;
+            sh.fn[m_mine] = fn;
+            sh.p[m_mine] = X.p;
         }
         // the rows of step s + 2
         prefetch(Z, s + 2);
         if (SERVED) cancel_probe(J, sh, s);
         __syncthreads();
-        const Decision dn = decide(sh.S, M, lane, cs.sse, co, KU, T, invT, X.N1, X.lnN1);
-        const double d_star = uniform_f64(sh.d[dn.ms]);
+        // every estimate's pixel and values with the sums, so that no second
+        // LDS trip follows the decision
+        const double dv = sh.d[lane], fv = sh.fn[lane];
+        const int32_t pv = sh.p[lane];
+        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
+        const double d_star = readlane_f64(dv, dn.ms);
         // an accepted zero change leaves image and residual as they are
         const bool changed = dn.accept && d_star != 0.0;
         if (changed && dn.ms == m_mine) {  // the owner of the winner applies Eq. 6
@@ -1589,28 +1775,25 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
                     }
                 }
             }
-            if (li == 0) {
-                J.f[X.p] = fn;
-                sh.pstar = X.p;
-                sh.fnstar = fn;
-            }
+            if (li == 0) J.f[X.p] = fn;
         }
-        count_decision(J, cs, dn, d_star, s);
-        if (dn.accept && dn.S != 0.0) co = sqrt(cs.sse / KU);  // C of Eq. 4 only moves with the SSE
+        if (traced) trace.add(J, dn, cs.sse, s, lane, KU);
+        count_decision(cs, dn, d_star);
         if (sizeof(Real) == 4 && J.resync_every > 0 && cs.since >= J.resync_every) {
             if (!RLDS) {
                 __syncthreads();
                 lds_residual_store<Real>(J, r, rl);
             }
             if (segmented) {  // the FP64 rebuild runs grid-wide between launches
+                trace_end(s + 1);
                 save_carry(J, cs, s + 1, true);
                 return true;
             }
             resync_in_group<Real, !RLDS, LenT>(J, cs, r, sh, lane, wave, NW);
-            co = sqrt(cs.sse / KU);
             if (!RLDS) lds_residual_load<Real>(J, r, rl);
             // the next two sets are drawn again after the rebuild, so that no
             // row stays in registers across it
+            draws_from(s + 1);
             prefetch(Y, s + 1);
             prefetch(Z, s + 2);
             table_slots(Y);
@@ -1624,8 +1807,8 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         }
         __syncthreads();
         if (changed) {
-            lp = uniform_i32(sh.pstar);
-            lfn = uniform_f64(sh.fnstar);
+            lp = __builtin_amdgcn_readlane(pv, dn.ms);
+            lfn = in_vector(readlane_f64(fv, dn.ms));
         } else {
             lp = -1;
         }
@@ -1647,31 +1830,43 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         return false;
     };
 
-    for (int64_t s = s_begin; s < n_steps;) {
-        if (step(A, B, C, s)) {
-            if (SERVED && cancelled) break;
-            return;
+    if (s_begin < n_steps) {
+        draws_from(s_begin);
+        prefetch(A, s_begin);
+        table_slots(A);
+#pragma unroll
+        for (int e = 0; e < E; ++e) A.rv[e] = in_lds(A.tk[e]) ? rl[A.tk[e] & ~kLdsFlag] : rget(gcol(A, e));
+        A.fo = J.f[A.p];
+        prefetch(B, s_begin + 1);
+        wait_loads();
+        for (int64_t s = s_begin;;) {
+            if (step(A, B, C, s)) {
+                if (SERVED && cancelled) break;
+                return;
+            }
+            if (++s >= n_steps) break;
+            if (step(B, C, A, s)) {
+                if (SERVED && cancelled) break;
+                return;
+            }
+            if (++s >= n_steps) break;
+            if (step(C, A, B, s)) {
+                if (SERVED && cancelled) break;
+                return;
+            }
+            if (++s >= n_steps) break;
         }
-        if (++s >= n_steps) break;
-        if (step(B, C, A, s)) {
-            if (SERVED && cancelled) break;
-            return;
-        }
-        if (++s >= n_steps) break;
-        if (step(C, A, B, s)) {
-            if (SERVED && cancelled) break;
-            return;
-        }
-        ++s;
     }
     if (!RLDS) {
         __syncthreads();
         lds_residual_store<Real>(J, r, rl);
     }
     if (segmented) {
+        trace_end(n_steps);
         save_carry(J, cs, n_steps, false);
         return;
     }
+    trace_end(cs.n_steps);
     write_stats(J, cs);
 }
 
@@ -1713,13 +1908,13 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
     Schedule sched;
     sched.start(s_begin, n_steps, J.n_stages, cs.T0, cs.TN, J.schedule);
 
+    // draws and rows ahead of their steps, as in the pipelined body: the
+    // draws in two stages, every load unconditional
     Draws cur, nxt;
-    auto fill = [&](Draws& D, int64_t base) {
-        D.base = base;
-        const int64_t s = base + lane;
+    auto draw = [&](Draws& D, int32_t block) {
+        const int64_t s = (int64_t)block * BL + lane;
+        D.drawn = block;
         D.p = 0;
-        D.n = 0;
-        D.b = 0;
         D.delta = 0.0;
         D.N1 = 0.0;
         D.lnN1 = 0.0;
@@ -1730,44 +1925,36 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
                 const Words4 w = philox4x64(k0, k1, (uint64_t)s, (uint64_t)wave, 0, 0);
                 D.p = J.support[__umul64hi(w.w0, (uint64_t)J.P)];
                 D.delta = J.delta_max * (2.0 * unit53(w.w1) - 1.0);
-                const int64_t b0 = J.row_ptr[D.p];
-                D.b = (uint32_t)b0;
-                D.n = (int32_t)(J.row_ptr[D.p + 1] - b0);
             }
             D.N1 = unit53(philox4x64(k0, k1, (uint64_t)s, 0, 1, 0).w0);
             D.lnN1 = log(D.N1);
         }
     };
-    cur.base = nxt.base = -1;
+    auto offsets = [&](Draws& D, int32_t block) {
+        D.block = block;
+        const int64_t b0 = J.row_ptr[D.p];
+        D.b = (uint32_t)b0;
+        D.n = active && (int64_t)block * BL + lane < n_steps ? (int32_t)(J.row_ptr[D.p + 1] - b0) : 0;
+    };
+    auto draws_from = [&](int64_t t) {
+        const int32_t block = (int32_t)(t / BL);
+        draw(cur, block);
+        offsets(cur, block);
+        nxt.drawn = nxt.block = -1;
+    };
     auto prefetch = [&](LongRow<Real, E>& S, int64_t t) {
-        if (t >= n_steps) {
-            S.p = 0;
-            S.n = 0;
-            S.b = 0;
-            S.delta = S.N1 = S.lnN1 = 0.0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                S.col[e] = 0;
-                S.len[e] = (Real)0;
-            }
-            return;
-        }
-        const int64_t base = t - t % BL;
-        if (cur.base != base) {
-            if (nxt.base == base)
-                cur = nxt;
-            else
-                fill(cur, base);
-        }
-        const int j = (int)(t - base);
-        if (j == BL / 2 && base + BL < n_steps) fill(nxt, base + BL);
-        S.p = __shfl(cur.p, j, kWave);
-        S.n = __shfl(cur.n, j, kWave);
-        const uint32_t b = (uint32_t)__shfl((int)cur.b, j, kWave);
+        const int32_t block = uniform_i32((int32_t)(t / BL));
+        if (cur.block != block) cur = nxt;
+        const int j = uniform_i32((int)t & (BL - 1));
+        if (j >= BL / 4 && nxt.drawn != block + 1) draw(nxt, block + 1);
+        if (j >= BL / 2 && nxt.block != block + 1) offsets(nxt, block + 1);
+        S.p = __builtin_amdgcn_readlane(cur.p, j);
+        S.n = __builtin_amdgcn_readlane(cur.n, j);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)cur.b, j);
         S.b = b;
-        S.delta = __shfl(cur.delta, j, kWave);
-        S.N1 = __shfl(cur.N1, j, kWave);
-        S.lnN1 = __shfl(cur.lnN1, j, kWave);
+        S.delta = in_vector(readlane_f64(cur.delta, j));
+        S.N1 = in_vector(readlane_f64(cur.N1, j));
+        S.lnN1 = in_vector(readlane_f64(cur.lnN1, j));
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int q = lane + e * kWave;
@@ -1794,19 +1981,45 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
     };
 
     LongRow<Real, E> A, B;
-    prefetch(A, s_begin);
     __syncthreads();  // setup (residual, LDS part, temperatures) complete
+    const double invKU = 1.0 / KU;
+    Trace trace{0.0, 0.0, 0, s_begin};
+    const bool traced = wave == 0 && (J.tr_m || J.tr_acc || J.tr_dc);
+    auto trace_end = [&](int64_t end) {  // before the chain, or its segment, ends
+        if (traced && trace.first < end) trace.store(J, end, lane, KU);
+    };
     bool cancelled = false;
     // returns true when the chain stops here (segment end or cancellation)
     auto step = [&](LongRow<Real, E>& X, LongRow<Real, E>& Y, int64_t s)
                     __attribute__((always_inline)) -> bool {
-        const double T = sched.at(s, n_steps, J.n_stages);
-        const double invT = 1.0 / T;
+        const double T = sched.at(s);
+        const double invT = sched.invT;
         prefetch(Y, s + 1);
+        // (loads unconditional; an entry in LDS reads the global value 0)
         Real rv[E];
         int li[E];
+        if constexpr (RLDS) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) rv[e] = rget(X.col[e], &li[e]);
+            for (int e = 0; e < E; ++e) rv[e] = rget(X.col[e], &li[e]);
+        } else {
+            Real gv[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int u = angle_of(J, X.col[e]), k = X.col[e] - u * J.K;
+                const bool in = u < J.UL;
+                const uint32_t at = in ? 0u : rpos(J, u, k);
+                li[e] = in ? u * J.Kc + (k - J.k_lo) : -1 - (int)at;
+                gv[e] = ld32((const Real*)r, at);
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) rv[e] = (Real)0;
+            if (J.UL > 0) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) rv[e] = rl[li[e] >= 0 ? li[e] : 0];
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) rv[e] = li[e] >= 0 ? rv[e] : gv[e];
+        }
         // (LATE) the lengths read back while the gathers are in flight
         Real ln[E];
 #pragma unroll
@@ -1835,11 +2048,11 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
             sh.S[wave] = (double)S;
             sh.d[wave] = d;
         }
-        const double co = sqrt(cs.sse / KU);
         if (SERVED) cancel_probe(J, sh, s);
         __syncthreads();
-        const Decision dn = decide(sh.S, M, lane, cs.sse, co, KU, T, invT, X.N1, X.lnN1);
-        const double d_star = uniform_f64(sh.d[dn.ms]);
+        const double dv = sh.d[lane];  // with the sums, so that no second LDS trip follows the decision
+        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
+        const double d_star = readlane_f64(dv, dn.ms);
         const bool changed = dn.accept && d_star != 0.0;
         if (changed && dn.ms == wave) {  // the owner of the winner applies Eq. 6
 #pragma unroll
@@ -1869,13 +2082,15 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
             }
             if (lane == 0) J.f[X.p] = fn;
         }
-        count_decision(J, cs, dn, d_star, s);
+        if (traced) trace.add(J, dn, cs.sse, s, lane, KU);
+        count_decision(cs, dn, d_star);
         if (sizeof(Real) == 4 && J.resync_every > 0 && cs.since >= J.resync_every) {
             if (!RLDS) {
                 __syncthreads();
                 lds_residual_store<Real>(J, r, rl);
             }
             if (segmented) {
+                trace_end(s + 1);
                 save_carry(J, cs, s + 1, true);
                 return true;
             }
@@ -1891,26 +2106,33 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
         }
         return false;
     };
-    for (int64_t s = s_begin; s < n_steps;) {
-        if (step(A, B, s)) {
-            if (SERVED && cancelled) break;
-            return;
+    if (s_begin < n_steps) {
+        draws_from(s_begin);
+        prefetch(A, s_begin);
+        wait_loads();
+        for (int64_t s = s_begin;;) {
+            if (step(A, B, s)) {
+                if (SERVED && cancelled) break;
+                return;
+            }
+            if (++s >= n_steps) break;
+            if (step(B, A, s)) {
+                if (SERVED && cancelled) break;
+                return;
+            }
+            if (++s >= n_steps) break;
         }
-        if (++s >= n_steps) break;
-        if (step(B, A, s)) {
-            if (SERVED && cancelled) break;
-            return;
-        }
-        ++s;
     }
     if (!RLDS) {
         __syncthreads();
         lds_residual_store<Real>(J, r, rl);
     }
     if (segmented) {
+        trace_end(n_steps);
         save_carry(J, cs, n_steps, false);
         return;
     }
+    trace_end(cs.n_steps);
     write_stats(J, cs);
 }
 
