@@ -11,6 +11,16 @@
 // in LDS when they fit, else in global memory.  Pixels are drawn by the same
 // Philox4x64-10 as the annealing chain (key (seed, 0), counter (update, 0,
 // 3, 0)), uniform over the support.
+//
+// Only the projections (and the pixel's value) tie an update to the one
+// before.  Everything else is fetched ahead, so that no memory latency is
+// left in the sequence: the draws and row offsets of 64 updates at a time
+// (one a lane) a block ahead, a row's entries three updates ahead, its rays'
+// factors and measurements and the pixel's value two, the factors'
+// reciprocals one.  What remains is an LDS read, the quotient (by the
+// reciprocal, exact: see below), the 64-lane sum and an LDS write.
+// 64 x 64, 60 angles, FP64, 6456 updates: 14.2 -> 4.4 ms (2.2 -> 0.69 us per
+// update, about 200 instructions of one wavefront and 700 clocks of waits).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -59,7 +69,40 @@ __global__ __launch_bounds__(256) void seq_setup_kernel(int64_t G, const int64_t
     }
 }
 
-template <typename LenT, bool PCLDS>
+// x / w from inv = 1 / w correctly rounded: two corrections of the quotient
+// by its exact (fused) residual, the second from a quotient within an ulp,
+// give the correctly rounded quotient (Markstein, IBM J. Res. Dev. 34, 1990)
+// wherever nothing on the way under- or overflows; other operands divide.
+__device__ __forceinline__ double quotient(double x, double w, double inv)
+{
+    const double ax = fabs(x);
+    if (ax > 0x1p-900 && ax < 0x1p900 && w > 0x1p-100 && w < 0x1p100) {
+        double q = x * inv;
+        q = fma(fma(-q, w, x), inv, q);
+        return fma(fma(-q, w, x), inv, q);
+    }
+    return x / w;
+}
+
+template <int E>
+struct SeqRow {  // one update: its pixel, and per lane up to E entries of its row
+    int64_t b, n;
+    int32_t p;
+    int32_t g[E];
+    double l[E], w[E], s[E], inv[E];
+    double fo;
+};
+
+// The wavefront's LDS writes before its LDS reads after this point (one
+// wavefront's LDS operations complete in order; this orders the compiler)
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename LenT, bool PCLDS, int E>
 __global__ __launch_bounds__(64) void sirt_seq_kernel(SeqArgs A)
 {
     extern __shared__ __align__(16) char lds[];
@@ -72,26 +115,124 @@ __global__ __launch_bounds__(64) void sirt_seq_kernel(SeqArgs A)
     }
     const LenT* len = (const LenT*)A.len;
     const double scale = A.lambda / (double)A.U;
-    for (int32_t n = 0; n < A.n_iter; ++n) {
-        for (int64_t m = 0; m < A.m_per; ++m) {
-            const uint64_t t = (uint64_t)n * (uint64_t)A.m_per + (uint64_t)m;
-            const Words4 w = philox4x64(A.seed, 0, t, 0, 3, 0);
-            const int32_t p = A.support[__umul64hi(w.w0, (uint64_t)A.P)];
-            const int64_t b = A.row_ptr[p], e = A.row_ptr[p + 1];
-            double part = 0.0;
-            for (int64_t q = b + lane; q < e; q += kWave) {
-                const int32_t g = A.col[q];
-                const double wg = A.W[g];
-                if (wg > 0.0) part = part + ((double)len[q] * (A.sino[g] - pc[g])) / wg;
-            }
-            const double df = scale * wave_canon_sum(part);
-            if (lane == 0) A.f[p] = A.f[p] + df;
-            for (int64_t q = b + lane; q < e; q += kWave) {
-                const int32_t g = A.col[q];
-                pc[g] = pc[g] + df * (double)len[q];
-            }
-            __syncthreads();  // this update's projections before the next reads them
+    const int64_t total = (int64_t)A.n_iter * A.m_per;
+
+    // draws of updates base .. base + 63, one a lane
+    struct Draws {
+        int64_t base, b, n;
+        int32_t p;
+    };
+    auto fill = [&](Draws& D, int64_t base) {
+        D.base = base;
+        D.p = 0;
+        D.b = D.n = 0;
+        if (base + lane < total) {
+            const Words4 w = philox4x64(A.seed, 0, (uint64_t)(base + lane), 0, 3, 0);
+            D.p = A.support[__umul64hi(w.w0, (uint64_t)A.P)];
+            D.b = A.row_ptr[D.p];
+            D.n = A.row_ptr[D.p + 1] - D.b;
         }
+    };
+    Draws cur, nxt;
+    cur.base = nxt.base = -1;
+    // the row of update t: its entries (past the row: the array's first)
+    auto fetch_row = [&](SeqRow<E>& R, int64_t t) {
+        R.p = 0;
+        R.b = R.n = 0;
+        if (t < total) {
+            const int64_t base = t & ~(int64_t)(kWave - 1);
+            const int j = (int)(t - base);
+            if (cur.base != base) {
+                if (nxt.base == base)
+                    cur = nxt;
+                else
+                    fill(cur, base);
+            }
+            if (j == kWave / 2 && base + kWave < total) fill(nxt, base + kWave);
+            R.p = __builtin_amdgcn_readlane(cur.p, j);
+            R.b = readlane_i64(cur.b, j);
+            R.n = readlane_i64(cur.n, j);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int64_t q = lane + e * kWave;
+            const int64_t at = q < R.n ? R.b + q : 0;
+            R.g[e] = A.col[at];
+            R.l[e] = (double)len[at];
+        }
+    };
+    auto fetch_rays = [&](SeqRow<E>& R) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            R.w[e] = A.W[R.g[e]];
+            R.s[e] = A.sino[R.g[e]];
+        }
+        R.fo = A.f[R.p];
+    };
+    auto reciprocals = [&](SeqRow<E>& R) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) R.inv[e] = 1.0 / R.w[e];
+    };
+
+    // the pixels of the last two updates and their values, which an earlier
+    // fetch of f cannot hold
+    int32_t p1 = -1, p2 = -1;
+    double f1 = 0.0, f2 = 0.0;
+    int64_t left = A.m_per;  // updates to the end of the iteration
+    int32_t it = 0;
+    // update t: X its row, complete; Y, Z, V the rows of t + 1, t + 2, t + 3
+    auto step = [&](SeqRow<E>& X, SeqRow<E>& Y, SeqRow<E>& Z, SeqRow<E>& V, int64_t t)
+                    __attribute__((always_inline)) {
+        double c[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) c[e] = pc[X.g[e]];
+        fetch_row(V, t + 3);
+        fetch_rays(Z);
+        double part = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + e * kWave < X.n && X.w[e] > 0.0)
+                part = part + quotient(X.l[e] * (X.s[e] - c[e]), X.w[e], X.inv[e]);
+        for (int64_t q = X.b + E * kWave + lane; q < X.b + X.n; q += kWave) {  // beyond the registers
+            const int32_t g = A.col[q];
+            const double wg = A.W[g];
+            if (wg > 0.0) part = part + ((double)len[q] * (A.sino[g] - pc[g])) / wg;
+        }
+        const double df = scale * wave_canon_sum(part);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + e * kWave < X.n) pc[X.g[e]] = c[e] + df * X.l[e];
+        for (int64_t q = X.b + E * kWave + lane; q < X.b + X.n; q += kWave) {
+            const int32_t g = A.col[q];
+            pc[g] = pc[g] + df * (double)len[q];
+        }
+        if (PCLDS)
+            wave_order();
+        else
+            __syncthreads();  // this update's projections before the next reads them
+        const double fo = X.p == p1 ? f1 : (X.p == p2 ? f2 : X.fo);
+        p2 = p1;
+        f2 = f1;
+        p1 = X.p;
+        f1 = fo + df;
+        if (lane == 0) A.f[X.p] = f1;
+        reciprocals(Y);
+        if (--left == 0) {
+            left = A.m_per;
+            if (A.cost) {
+                double sq = 0.0;
+#pragma unroll 8
+                for (int64_t g = lane; g < G; g += kWave) {
+                    const double d = pc[g] - A.sino[g];
+                    sq = sq + d * d;
+                }
+                sq = wave_canon_sum(sq);
+                if (lane == 0) A.cost[it] = sqrt(sq / ((double)A.K * (double)A.U));
+            }
+            ++it;
+        }
+    };
+    if (total == 0) {  // iterations without updates: the cost of the start
         if (A.cost) {
             double sq = 0.0;
             for (int64_t g = lane; g < G; g += kWave) {
@@ -99,9 +240,42 @@ __global__ __launch_bounds__(64) void sirt_seq_kernel(SeqArgs A)
                 sq = sq + d * d;
             }
             sq = wave_canon_sum(sq);
-            if (lane == 0) A.cost[n] = sqrt(sq / ((double)A.K * (double)A.U));
+            for (int32_t n = lane; n < A.n_iter; n += kWave) A.cost[n] = sqrt(sq / ((double)A.K * (double)A.U));
         }
+        return;
     }
+    SeqRow<E> R0, R1, R2, R3;
+    fetch_row(R0, 0);
+    fetch_row(R1, 1);
+    fetch_row(R2, 2);
+    fetch_rays(R0);
+    fetch_rays(R1);
+    reciprocals(R0);
+    for (int64_t t = 0; t < total;) {
+        step(R0, R1, R2, R3, t);
+        if (++t >= total) break;
+        step(R1, R2, R3, R0, t);
+        if (++t >= total) break;
+        step(R2, R3, R0, R1, t);
+        if (++t >= total) break;
+        step(R3, R0, R1, R2, t);
+        ++t;
+    }
+}
+
+template <typename LenT, int E>
+int32_t launch_seq(const SeqArgs& A, int64_t lds_bytes, hipStream_t st)
+{
+    if (lds_bytes > 0) {
+        const void* k = (const void*)sirt_seq_kernel<LenT, true, E>;
+        PILA_TRY(set_lds(k, (int)lds_bytes));
+        SeqArgs args = A;
+        void* argv[] = {&args};
+        PILA_HIP(hipLaunchKernel(k, dim3(1), dim3(kWave), argv, (size_t)lds_bytes, st));
+    } else {
+        sirt_seq_kernel<LenT, false, E><<<1, kWave, 0, st>>>(A);
+    }
+    return PILA_OK;
 }
 
 size_t seq_bytes(const pila_geom* g, int32_t n_iter)
@@ -140,14 +314,15 @@ int32_t seq_impl(const pila_geom* geom, const pila_csr* csr, const double* d_sin
     PILA_TRY(device_props(&prop));
     const int64_t budget = (int64_t)prop.sharedMemPerBlock - 1024;
     if (prm->n_iter > 0 && A.P > 0) {
-        if (G * 8 <= budget) {
-            const void* k = (const void*)sirt_seq_kernel<LenT, true>;
-            PILA_TRY(set_lds(k, (int)(G * 8)));
-            void* args[] = {&A};
-            PILA_HIP(hipLaunchKernel(k, dim3(1), dim3(kWave), args, (size_t)(G * 8), st));
-        } else {
-            sirt_seq_kernel<LenT, false><<<1, kWave, 0, st>>>(A);
-        }
+        // entries per lane in registers: the smallest that holds the longest
+        // row (rows beyond 256 entries read the rest in place)
+        const int64_t lds = G * 8 <= budget ? G * 8 : 0;
+        if (csr->max_row <= kWave)
+            PILA_TRY((launch_seq<LenT, 1>(A, lds, st)));
+        else if (csr->max_row <= 2 * kWave)
+            PILA_TRY((launch_seq<LenT, 2>(A, lds, st)));
+        else
+            PILA_TRY((launch_seq<LenT, 4>(A, lds, st)));
     }
     PILA_HIP(hipGetLastError());
     if (h_cost && prm->n_iter > 0) {
