@@ -2,9 +2,9 @@
 // (section III-D, Eq. 10-11) on gfx950.
 //
 // Both directions are gathers, never scatters: the forward projection walks
-// the ray-major copy of the PILA (one wavefront per ray, lanes stride over
-// the ray's entries, FP64 accumulation, shuffle reduction), the back
-// projection walks the pixel-major copy (one wavefront per pixel).  Every
+// the ray-major copy of the PILA (a wavefront per few neighbouring rays, lanes
+// stride over the rays' entries, FP64 accumulation, shuffle reduction), the
+// back projection walks the pixel-major copy (a wavefront per few pixels).  Every
 // output is produced by exactly one wavefront in a fixed order, so results
 // are deterministic and need no atomics.  Both stream the PILA from HBM
 // once per call (the image / sinogram being gathered stays in L2 / MALL):
@@ -20,103 +20,122 @@ namespace pila {
 
 namespace {
 
-constexpr int kGatherBlocks = 4096;  // fixed grid: reduction order does not depend on sizes
+constexpr int kGatherBlocks = 4096;  // largest grid of the per-row kernels
 constexpr int kWPB = 4;              // wavefronts per block
-
-enum { kFwd = 0, kResW = 1, kW = 2 };
-
-// This lane's share of one CSR row's dot product with a gathered vector x
-// (or, SQUARES, of the row's squared lengths): entries q = b + lane + 64 i in
-// ascending i, fused multiply-add in FP64.  kU entries are loaded before any
-// is used, so each lane keeps kU row loads and kU gathers in flight.
-constexpr int kU = 8;
-
-template <typename LenT, bool SQUARES>
-__device__ __forceinline__ double row_dot(int64_t b, int64_t e, int lane,
-                                          const int32_t* __restrict__ ci,
-                                          const LenT* __restrict__ ln,
-                                          const double* __restrict__ x)
-{
-    double acc = 0.0;
-    for (int64_t q0 = b + lane; q0 < e; q0 += 64 * kU) {
-        double l[kU], v[kU];
-        int32_t c[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int64_t q = q0 + 64 * u < e ? q0 + 64 * u : b;
-            l[u] = (double)ln[q];
-            if (!SQUARES) c[u] = ci[q];
-        }
-        if (!SQUARES) {
-#pragma unroll
-            for (int u = 0; u < kU; ++u) v[u] = x[c[u]];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (q0 + 64 * u < e) acc = fma(l[u], SQUARES ? l[u] : v[u], acc);
-    }
-    return acc;
-}
 
 // Rows [0, n) in 8 contiguous chunks, one per XCD: the dispatcher hands
 // workgroups to the 8 XCDs round robin (workgroup b to XCD b mod 8), so the
 // workgroups of one XCD take neighbouring rays (or pixels), whose gathers
 // touch the same image (or sinogram) lines and hit that XCD's L2.  Within a
-// chunk the XCD's wavefronts stride over the rows.  The grid is a multiple
-// of 8; each row still has exactly one wavefront.
+// chunk the XCD's wavefronts stride over groups of R rows.  The grid is a
+// multiple of 8; each row has exactly one wavefront.
 struct XcdRows {
     int64_t first, end, stride;
 };
 
+template <int R>
 __device__ __forceinline__ XcdRows xcd_rows(int64_t n, int w)
 {
     constexpr int kXcd = 8;
     const int x = blockIdx.x % kXcd;
     const int64_t nb = gridDim.x / kXcd;
-    const int64_t chunk = (n + kXcd - 1) / kXcd;
+    const int64_t chunk = ((n + kXcd - 1) / kXcd + R - 1) / R * R;
     const int64_t lo = x * chunk;
     const int64_t hi = lo + chunk < n ? lo + chunk : n;
-    return {lo + (int64_t)(blockIdx.x / kXcd) * kWPB + w, hi, nb * kWPB};
+    return {lo + ((int64_t)(blockIdx.x / kXcd) * kWPB + w) * R, hi, nb * kWPB * R};
 }
 
-// The same dot product for a ray closer to the image's columns than to its
-// rows (|cos| > |sin|): its consecutive entries are pixels of consecutive
-// image rows, so the image is read transposed (fT[j N + i] = f[i N + j]),
-// where they are neighbours.  Same entries, lanes and order as row_dot.
-template <typename LenT>
-__device__ __forceinline__ double row_dot_t(int64_t b, int64_t e, int lane,
-                                            const int32_t* __restrict__ ci,
-                                            const LenT* __restrict__ ln,
-                                            const double* __restrict__ fT, int N, double invN)
+// out[g] = sum over CSR row g of length times x[index] (FP64, fused
+// multiply-add).  A wavefront takes 8 neighbouring rows, 8 lanes each, and a
+// lane V consecutive entries at a time: lane e of a row the entries
+// e V + 8 V i .. + V - 1 by ascending i; its sum is added to the other
+// lanes' by a butterfly.  A row's consecutive entries lie on a line of x
+// each (a pixel's on another sinogram row per angle, a steep ray's on another
+// image row each), while neighbouring rows' entries lie on the same lines, so
+// a gather of 8 rows x 8 entries meets about 10 lines where one row's 64
+// entries meet 64, and a line's 8 values come from one access; it is the
+// accesses of a CU's address path that bound this kernel.  The next entries
+// are loaded while the gathers are in flight.
+// 1024 x 1024, 720 angles, FP32 (7.6e8 entries, 6 GB; one access a lane alone
+// would be 1.3 ms): forward 4.05 -> 2.11 ms, back 4.85 -> 2.66 ms; 256 x 256 x
+// 180: 45 -> 31 and 56 -> 31 us.  (Eight rows at once but 64 lanes on each:
+// 2.41 and 2.94 ms.)
+template <typename LenT, int V>
+__global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                         const int32_t* __restrict__ ci,
+                                                         const LenT* __restrict__ ln,
+                                                         const double* __restrict__ x, double* __restrict__ out)
 {
-    double acc = 0.0;
-    for (int64_t q0 = b + lane; q0 < e; q0 += 64 * kU) {
-        double l[kU], v[kU];
-        int32_t c[kU];
+    constexpr int R = 8, L = 64 / R;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const XcdRows xr = xcd_rows<R>(n, w);
+    struct Entries {
+        int32_t c[V];
+        LenT l[V];
+    };
+    for (int64_t g = xr.first; g < xr.end; g += xr.stride) {
+        const int64_t row = g + lane / L;
+        const bool on = row < xr.end;
+        const int64_t end = on ? rp[row + 1] : 0;
+        int64_t q = (on ? rp[row] : 0) + lane % L * V;
+        double acc = 0.0;
+        Entries e;
+        int64_t at = 0;
+        auto load = [&]() {  // V entries in one load each, from q or the last V of the array
+            at = q < nnz - V ? q : nnz - V;
+            __builtin_memcpy(e.c, ci + at, sizeof(e.c));
+            __builtin_memcpy(e.l, ln + at, sizeof(e.l));
+        };
+        if (q < end) load();
+        while (q < end) {
+            double f[V];
+            LenT k[V];
+            bool mine[V];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int64_t q = q0 + 64 * u < e ? q0 + 64 * u : b;
-            l[u] = (double)ln[q];
-            c[u] = ci[q];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            int i = (int)((double)c[u] * invN);  // c / N, then corrected
-            int j = c[u] - i * N;
-            if (j < 0) {
-                --i;
-                j += N;
-            } else if (j >= N) {
-                ++i;
-                j -= N;
+            for (int v = 0; v < V; ++v) {
+                mine[v] = at + v >= q && at + v < end;
+                f[v] = x[e.c[v]];
+                k[v] = e.l[v];
             }
-            v[u] = fT[j * N + i];
+            __builtin_amdgcn_sched_barrier(0);
+            q += L * V;
+            if (q < end) load();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const double sum = fma((double)k[v], f[v], acc);
+                acc = mine[v] ? sum : acc;
+            }
         }
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (q0 + 64 * u < e) acc = fma(l[u], v[u], acc);
+        for (int s = 1; s < L; s <<= 1) acc += __shfl_xor(acc, s, 64);
+        if (on && lane % L == 0) out[row] = acc;
     }
-    return acc;
+}
+
+// W[g] = sum of the squared lengths of CSR row g, in the same order
+template <typename LenT>
+__global__ __launch_bounds__(256) void row_squares_kernel(int64_t n, const int64_t* __restrict__ rp,
+                                                          const LenT* __restrict__ ln, double* __restrict__ W)
+{
+    constexpr int kU = 8;  // entries per lane in flight
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const XcdRows xr = xcd_rows<1>(n, w);
+    for (int64_t g = xr.first; g < xr.end; g += xr.stride) {
+        const int64_t b = rp[g], e = rp[g + 1];
+        double acc = 0.0;
+        for (int64_t q0 = b + lane; q0 < e; q0 += 64 * kU) {
+            double l[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) l[u] = (double)ln[q0 + 64 * u < e ? q0 + 64 * u : b];
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (q0 + 64 * u < e) acc = fma(l[u], l[u], acc);
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) W[g] = acc;
+    }
 }
 
 // fT = f transposed (N x N), 32 x 32 tiles through LDS
@@ -137,55 +156,6 @@ __global__ __launch_bounds__(256) void transpose_kernel(int N, const double* __r
     }
 }
 
-template <typename LenT, int MODE>
-__global__ __launch_bounds__(256) void ray_gather_kernel(int64_t G, const int64_t* __restrict__ rp,
-                                                         const int32_t* __restrict__ ci,
-                                                         const LenT* __restrict__ ln,
-                                                         const double* __restrict__ f,
-                                                         const double* __restrict__ sino,
-                                                         const double* __restrict__ W,
-                                                         double* __restrict__ out,
-                                                         double* __restrict__ partial,
-                                                         const double* __restrict__ fT = nullptr,
-                                                         const double* __restrict__ trig = nullptr,
-                                                         int N = 0, int K = 1)
-{
-    __shared__ double wpart[kWPB];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double sq = 0.0;  // lane 0: this wavefront's sum of squared residuals
-    const XcdRows xr = xcd_rows(G, w);
-    const double invN = N > 0 ? 1.0 / (double)N : 0.0;
-    for (int64_t g = xr.first; g < xr.end; g += xr.stride) {
-        const int64_t b = rp[g], e = rp[g + 1];
-        bool cols = false;
-        if (MODE != kW && fT) {
-            const int64_t u = g / K;
-            cols = fabs(trig[2 * u]) > fabs(trig[2 * u + 1]);
-        }
-        const double acc = wave_sum(cols ? row_dot_t<LenT>(b, e, lane, ci, ln, fT, N, invN)
-                                         : row_dot<LenT, MODE == kW>(b, e, lane, ci, ln, f));
-        if (lane == 0) {
-            if (MODE == kResW) {
-                const double res = sino[g] - acc;
-                const double wg = W[g];
-                out[g] = wg > 0.0 ? res / wg : 0.0;
-                sq += res * res;
-            } else {
-                out[g] = acc;
-            }
-        }
-    }
-    if (MODE == kResW) {
-        if (lane == 0) wpart[w] = sq;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double s = 0.0;
-            for (int q = 0; q < kWPB; ++q) s += wpart[q];
-            partial[blockIdx.x] = s;
-        }
-    }
-}
-
 // one workgroup: out[0] = sum of partial[0..n) in a fixed order
 __global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ partial, int n,
                                                      double* __restrict__ out)
@@ -197,30 +167,6 @@ __global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ 
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) out[0] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
-}
-
-enum { kBack = 0, kSirt = 1 };
-
-template <typename LenT, int MODE>
-__global__ __launch_bounds__(256) void pixel_gather_kernel(int64_t NP, const int64_t* __restrict__ rp,
-                                                           const int32_t* __restrict__ ci,
-                                                           const LenT* __restrict__ ln,
-                                                           const double* __restrict__ y,
-                                                           double* __restrict__ out, double scale)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const XcdRows xr = xcd_rows(NP, w);
-    for (int64_t p = xr.first; p < xr.end; p += xr.stride) {
-        const int64_t b = rp[p], e = rp[p + 1];
-        if (MODE == kSirt && b == e) continue;
-        const double acc = wave_sum(row_dot<LenT, false>(b, e, lane, ci, ln, y));
-        if (lane == 0) {
-            if (MODE == kSirt)
-                out[p] = out[p] + scale * acc;
-            else
-                out[p] = acc;
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -767,11 +713,32 @@ SirtLayout sirt_layout(const pila_geom* g, int32_t n_iter, size_t n_tiles)
     return L;
 }
 
-unsigned gather_blocks(int64_t rows)
+unsigned gather_blocks(int64_t groups)
 {
-    int64_t b = (rows + kWPB - 1) / kWPB;
+    int64_t b = (groups + kWPB - 1) / kWPB;
     b = b < kGatherBlocks ? b : kGatherBlocks;
     return (unsigned)((b + 7) / 8 * 8);  // a multiple of the 8 XCDs, at least 8
+}
+
+template <typename LenT>
+int32_t gather_rows(int64_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const void* ln, const double* x,
+                    double* out, hipStream_t st)
+{
+    const unsigned blocks = gather_blocks((n + 7) / 8);
+    if (nnz >= 4)
+        row_gather_kernel<LenT, 4><<<blocks, 256, 0, st>>>(n, nnz, rp, ci, (const LenT*)ln, x, out);
+    else
+        row_gather_kernel<LenT, 1><<<blocks, 256, 0, st>>>(n, nnz, rp, ci, (const LenT*)ln, x, out);
+    PILA_HIP(hipGetLastError());
+    return PILA_OK;
+}
+
+int32_t gather_rows(int32_t len_dtype, int64_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const void* ln,
+                    const double* x, double* out, hipStream_t st)
+{
+    if (len_dtype == PILA_F64) return gather_rows<double>(n, nnz, rp, ci, ln, x, out, st);
+    if (len_dtype == PILA_F32) return gather_rows<float>(n, nnz, rp, ci, ln, x, out, st);
+    return gather_rows<LenQ>(n, nnz, rp, ci, ln, x, out, st);
 }
 
 int32_t check_csr(const pila_geom* g, const pila_csr* c, bool need_rays, bool need_pixels)
@@ -797,19 +764,8 @@ extern "C" int32_t pila_forward(const pila_geom* geom, const pila_csr* csr, cons
     clear_error();
     PILA_TRY(check_csr(geom, csr, true, false));
     if (!d_image || !d_out) return fail(PILA_EINVAL, "image or output is NULL");
-    const int64_t G = (int64_t)geom->n_angles * geom->n_bins;
-    hipStream_t st = (hipStream_t)stream;
-    if (geom->len_dtype == PILA_F64)
-        ray_gather_kernel<double, kFwd><<<gather_blocks(G), 256, 0, st>>>(
-            G, csr->t_row_ptr, csr->t_col, (const double*)csr->t_len, d_image, nullptr, nullptr, d_out, nullptr);
-    else if (geom->len_dtype == PILA_F32)
-        ray_gather_kernel<float, kFwd><<<gather_blocks(G), 256, 0, st>>>(
-            G, csr->t_row_ptr, csr->t_col, (const float*)csr->t_len, d_image, nullptr, nullptr, d_out, nullptr);
-    else
-        ray_gather_kernel<LenQ, kFwd><<<gather_blocks(G), 256, 0, st>>>(
-            G, csr->t_row_ptr, csr->t_col, (const LenQ*)csr->t_len, d_image, nullptr, nullptr, d_out, nullptr);
-    PILA_HIP(hipGetLastError());
-    return PILA_OK;
+    return gather_rows(geom->len_dtype, (int64_t)geom->n_angles * geom->n_bins, csr->nnz, csr->t_row_ptr, csr->t_col,
+                       csr->t_len, d_image, d_out, (hipStream_t)stream);
 }
 
 extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, const double* d_sino,
@@ -818,19 +774,8 @@ extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, 
     clear_error();
     PILA_TRY(check_csr(geom, csr, false, true));
     if (!d_sino || !d_out) return fail(PILA_EINVAL, "sinogram or output is NULL");
-    const int64_t NP = (int64_t)geom->n * geom->n;
-    hipStream_t st = (hipStream_t)stream;
-    if (geom->len_dtype == PILA_F64)
-        pixel_gather_kernel<double, kBack><<<gather_blocks(NP), 256, 0, st>>>(
-            NP, csr->row_ptr, csr->col, (const double*)csr->len, d_sino, d_out, 0.0);
-    else if (geom->len_dtype == PILA_F32)
-        pixel_gather_kernel<float, kBack><<<gather_blocks(NP), 256, 0, st>>>(
-            NP, csr->row_ptr, csr->col, (const float*)csr->len, d_sino, d_out, 0.0);
-    else
-        pixel_gather_kernel<LenQ, kBack><<<gather_blocks(NP), 256, 0, st>>>(
-            NP, csr->row_ptr, csr->col, (const LenQ*)csr->len, d_sino, d_out, 0.0);
-    PILA_HIP(hipGetLastError());
-    return PILA_OK;
+    return gather_rows(geom->len_dtype, (int64_t)geom->n * geom->n, csr->nnz, csr->row_ptr, csr->col, csr->len, d_sino, d_out,
+                       (hipStream_t)stream);
 }
 
 extern "C" int32_t sirt_workspace_size(const pila_geom* geom, const sirt_params* params, size_t* bytes)
@@ -869,7 +814,6 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     LenT* l0 = (LenT*)(ws + L.l0);
     LenT* l1 = (LenT*)(ws + L.l1);
     int32_t* base = (int32_t*)(ws + L.base);
-    const unsigned gb = gather_blocks(G);
     // PILA_SIRT_CSR=1 sums every tile from its CSR rows (the path a tile of
     // irregular shape takes), for tests of that path
     const char* env = std::getenv("PILA_SIRT_CSR");
@@ -877,9 +821,7 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     const bool reuse = (prm->flags & PILA_SIRT_REUSE_LAYOUT) != 0;
     // factor matrix: W_g = sum of squared lengths of ray g over the support
     if (!reuse)
-        ray_gather_kernel<LenT, kW><<<gb, 256, 0, st>>>(G, csr->t_row_ptr, csr->t_col,
-                                                        (const LenT*)csr->t_len, nullptr, nullptr,
-                                                        nullptr, W, nullptr);
+        row_squares_kernel<LenT><<<gather_blocks(G), 256, 0, st>>>(G, csr->t_row_ptr, (const LenT*)csr->t_len, W);
     if (n_tiles > 0 && !reuse) {
         PILA_HIP(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int32_t) * tiles.size(),
                                 hipMemcpyHostToDevice, st));
