@@ -406,9 +406,9 @@ typedef struct sirt_params {
 
 /* sirt_workspace_size - device workspace bytes that sirt_run needs: the
  * factor matrix, residuals and partial sums, the transposed image and the two
- * tile layouts sirt_run builds from the PILA (about 9 bytes per (pixel,
- * angle) of the support's 8 x 8 tiles and 9 bytes per (ray, image row or
- * column) in FP32; 15 GB at 1024 x 1024 and 720 angles). */
+ * tile layouts sirt_run builds from the PILA (room for two lengths per (pixel,
+ * angle) of the support's 8 x 8 tiles and per (ray, image row or column),
+ * about 8.4 bytes each in FP32; 14 GB at 1024 x 1024 and 720 angles). */
 int32_t sirt_workspace_size(const pila_geom* geom, const sirt_params* params, size_t* bytes);
 
 /*

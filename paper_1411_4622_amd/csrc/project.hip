@@ -9,7 +9,6 @@
 // are deterministic and need no atomics.  Both stream the PILA from HBM
 // once per call (the image / sinogram being gathered stays in L2 / MALL):
 // these are HBM-bound kernels.
-#include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <vector>
@@ -157,8 +156,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(int N, const double* __r
 }
 
 // one workgroup: out[0] = sum of partial[0..n) in a fixed order
-__global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ partial, int n,
-                                                     double* __restrict__ out)
+__device__ __forceinline__ void sum_partials(const double* __restrict__ partial, int n, double* __restrict__ out)
 {
     __shared__ double ws[4];
     double s = 0.0;
@@ -171,30 +169,42 @@ __global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Tile layouts for SIRT.  Both projections run one wavefront per tile of 64
-// PILA rows (lane = row) and walk the tile's rows in step: at one step each
-// lane holds at most two entries, at neighbouring indices, stored as an
-// 8-bit offset from the step's smallest index (one base per step) and two
-// lengths, zero where absent.  Element (t, s, lane) sits at (t S + s) 64 +
-// lane, so the 64 lanes of a step read consecutive bytes and words.  A tile
-// whose rows break that shape (a third entry at one step, a pair that is
-// not neighbours, an offset above 255) is flagged and its rows are summed
-// straight from the CSR.
+// PILA rows (lane = row) and walk the tile's rows in step.
 //
 // Back projection: tiles of 8 x 8 pixels, steps = angles.  A pixel's shadow
-// on the detector is at most sqrt 2 bins wide, so at one angle it meets one
-// or two rays of neighbouring bins, and the tile's 64 pixels meet about 12
-// bins of one sinogram row.  Each pixel adds its terms in its row's order
-// (angle, then bin), as a walk of the row would.
-//
+// on the detector is at most sqrt 2 bins wide, so at one angle it meets at
+// most the two bins b, b + 1 with b = floor(its centre's projection); the
+// tile's 64 pixels meet about 12 bins of one sinogram row.
 // Forward projection: tiles of 64 rays of consecutive bins at one angle;
-// steps are image rows for rays closer to the columns (|cos| > |sin|), image
-// columns for the others.  Such a ray moves less than one pixel sideways per
-// step, so it meets one or two neighbouring pixels there, and the tile's 64
-// rays meet about 64-91 pixels of one image row (read from the image) or
-// column (read from its transpose).  Steps run over the tile's used range.
+// steps are image rows for rays closer to the columns (|cos| >= |sin|), image
+// columns for the others.  There a ray meets at most the two pixels b, b + 1
+// next to its centre, and the tile's 64 rays meet about 64-91 pixels of one
+// image row (read from the image) or column (read from its transpose).
+//
+// b follows from the geometry (two or three FP64 operations), so a step
+// stores only which lanes have the entry at b and which the one at b + 1 (two
+// 64-bit masks) and where its lengths begin; the lengths themselves are
+// packed in lane order, a lane's one at b before its one at b + 1.  So a lane
+// takes one load for its lengths and one for its values at a step, neither
+// waiting for the other, and the wavefront reads the lengths as one run.  Per
+// entry that is 4.4 bytes in FP32 (with the headers), where an offset and two
+// lengths per (row, step), absent ones among them, took 7.1 (back) and 9.5
+// (forward) and five loads: the loads a CU's address path takes bound both.
+// Every entry is added in the order of a walk by step, b before b + 1.
+//
+// The layout is built from the PILA's entries and holds their lengths; a tile
+// with an entry that is not at b or b + 1 (or two at one place) is flagged and
+// its rows are summed straight from the CSR.
+// 1024 x 1024, 720 angles, FP32: forward 1.354 -> 0.940 ms, back 1.323 -> 0.939
+// ms an iteration (3.3 GB each, 3.5 TB/s, address path 80% busy).
 // ---------------------------------------------------------------------------
 constexpr int kTile = 8;
 constexpr int kOdd = -2;  // flag of a tile summed from its CSR rows
+
+struct StepHead {
+    uint64_t m0, m1;  // lanes with an entry at b, at b + 1
+    int32_t pos, pad; // the step's first length in its tile's array
+};
 
 __device__ __forceinline__ int64_t tile_pixel(const int32_t* tiles, int t, int lane, int N)
 {
@@ -206,252 +216,376 @@ __device__ __forceinline__ int64_t tile_pixel(const int32_t* tiles, int t, int l
 
 __device__ __forceinline__ bool ray_cols(const double* trig, int u)
 {
-    return fabs(trig[2 * u]) > fabs(trig[2 * u + 1]);
+    return fabs(trig[2 * u]) >= fabs(trig[2 * u + 1]);
 }
 
-// A lane's window of kWin consecutive PILA entries (index and length) in
-// LDS, aligned to kWin entries.  A tile build walks 64 rows at once, one per
-// lane, a few entries per step; read straight from memory each entry would
-// cost a cache line that is evicted again before the lane's next step.
-// Through the window each 64-byte segment is fetched once.
-constexpr int kWin = 16;
-
-template <typename LenT>
-struct EntryWindow {
-    int32_t* wc;  // LDS, kWin indices of this lane
-    LenT* wl;     // LDS, kWin lengths
-    int64_t w;    // first entry held
-    const int32_t* __restrict__ ci;
-    const LenT* __restrict__ ln;
-    int64_t nnz;
-    bool vec;  // ci and ln 16-byte aligned: fill with 16-byte loads
-    __device__ void fill(int64_t q)
+// b of a row at a step.  The layout's builder and its readers call the same
+// functions on the same values, so they agree on b whatever its rounding.
+struct PixelRow {  // pixel (xc, yc); step = angle
+    double xc, yc, cK;
+    __device__ __forceinline__ PixelRow(int N, int K, int64_t p)
     {
-        w = q & ~(int64_t)(kWin - 1);
-        if (vec && w + kWin <= nnz) {
-            const int4* c4 = reinterpret_cast<const int4*>(ci + w);
-#pragma unroll
-            for (int a = 0; a < kWin / 4; ++a) {
-                const int4 v = c4[a];
-                wc[4 * a] = v.x;
-                wc[4 * a + 1] = v.y;
-                wc[4 * a + 2] = v.z;
-                wc[4 * a + 3] = v.w;
-            }
-            constexpr int kPer = 16 / (int)sizeof(LenT);
-            const int4* l4 = reinterpret_cast<const int4*>(ln + w);
-#pragma unroll
-            for (int a = 0; a < kWin / kPer; ++a) {
-                const int4 v = l4[a];
-                __builtin_memcpy(wl + a * kPer, &v, 16);
-            }
+        const int i = p >= 0 ? (int)(p / N) : 0, j = p >= 0 ? (int)(p - (int64_t)i * N) : 0;
+        xc = j - (0.5 * N - 0.5);
+        yc = (0.5 * N - 0.5) - i;
+        cK = 0.5 * (K - 1);
+    }
+    __device__ __forceinline__ int at(const double* trig, int u) const
+    {
+        return (int)floor(fma(xc, trig[2 * u], fma(yc, trig[2 * u + 1], cK)));
+    }
+};
+struct RayRow {  // ray k of an angle; step = image row or column
+    double slope, a0;
+    __device__ __forceinline__ RayRow(int N, int K, const double* trig, int u, int k)
+    {
+        const double c = trig[2 * u], s = trig[2 * u + 1], sk = k - 0.5 * (K - 1), hc = 0.5 * N - 0.5;
+        if (ray_cols(trig, u)) {
+            slope = s / c;
+            a0 = (sk - hc * s) / c + hc;
         } else {
-            for (int a = 0; a < kWin && w + a < nnz; ++a) {
-                wc[a] = ci[w + a];
-                wl[a] = ln[w + a];
-            }
+            slope = c / s;
+            a0 = hc - (sk + hc * c) / s;
         }
     }
-    __device__ int32_t col(int64_t q)
-    {
-        if (q < w || q >= w + kWin) fill(q);
-        return wc[q - w];
-    }
-    __device__ LenT len(int64_t q)
-    {
-        if (q < w || q >= w + kWin) fill(q);
-        return wl[q - w];
-    }
+    __device__ __forceinline__ int at(const double*, int x) const { return (int)floor(fma((double)x, slope, a0)); }
 };
 
-// LDS of the 64 lanes' windows (rows padded by one word against bank conflicts)
-template <typename LenT>
-struct WindowLds {
-    int32_t c[64][kWin + 1];
-    LenT l[64][kWin + 1];
-};
-
-template <typename LenT>
-__device__ __forceinline__ EntryWindow<LenT> entry_window(WindowLds<LenT>& lds, int lane,
-                                                          const int32_t* ci, const LenT* ln,
-                                                          int64_t nnz, bool vec)
+__device__ __forceinline__ int64_t lane0_i64(int64_t v)
 {
-    return EntryWindow<LenT>{lds.c[lane], lds.l[lane], -(int64_t)kWin - 1, ci, ln, nnz, vec};
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Walk of a PILA row in its stored order.
-struct RowWalk {
-    int64_t q, e;
-    __device__ bool more() const { return q < e; }
-    template <typename Win>
-    __device__ void next(Win&) { ++q; }
+// a / d for 0 <= a < 2^31 by the reciprocal (corrected)
+__device__ __forceinline__ int div_by(int a, int d, double inv)
+{
+    int q = (int)((double)a * inv);
+    const int r = a - q * d;
+    return r < 0 ? q - 1 : (r >= d ? q + 1 : q);
+}
+
+// Builds the layout of one tile per workgroup, a span of steps at a time.
+// The wavefronts take 16 rows each and collect the span's masks in LDS; the
+// steps' lengths get their places by a scan; the lengths go to their places
+// in LDS and leave in contiguous runs.  (Placed straight in memory, each
+// length touches a line of its own that is evicted before the next row's.)
+//
+// A row's entries are in the order of its steps, at most two a step, so a
+// span's are the next 2 kSpan at most: all 16 rows' are loaded at once and
+// stay in registers until they are placed.  Rays closer to the rows whose
+// columns fall as their rows rise are the exception (kRayDown): they are
+// taken from the last step to the first, and as each image row's run of
+// columns is stored left to right, a span rereads the run that its end cuts
+// and may pass two runs' entries of later spans.  With runs of up to 20
+// columns (|sin| <= 19 |cos|) that is at most 60 entries more, one more
+// window of 64; flatter rays are walked until no later row can reach the span.
+// 1024 x 1024, 720 angles, FP32 (6 GB read, 3.3 written a layout): 12.9 + 6.9
+// -> 6.2 + 4.3 ms (rays, pixels).  Placing the lengths straight in memory took
+// 21 + 15 ms, one row at a time 10 + 11.
+enum { kPixels = 0, kRayUp = 1, kRayDown = 2 };
+template <typename LenT>
+struct LayoutLds {
+    static constexpr int kSpan = sizeof(LenT) == 8 ? 32 : 64;  // steps whose lengths fill 32 KB
+    LenT stage[kSpan * 128];
+    unsigned long long mask[2][kSpan];
+    int64_t row_b[64];  // the tile's rows: first entry and length
+    int row_n[64];
+    int off[kSpan + 1];
+    int taken[2][64];  // per row: entries before its first one not taken, this span's and the next's
+    int bad, entries;
 };
 
-// Walk of a ray's entries in ascending step order.  Entries are stored by
-// ascending image row, then column.  Where the steps are image rows, or are
-// columns that rise with the rows, that order already is the step order;
-// for a ray whose columns fall as its rows rise, the walk takes the row
-// groups (entries of one image row) last to first, each first to last.
-struct RayWalk {
-    int N;
-    int64_t b, q, gs, ge;
-    bool rev;
-    template <typename Win>
-    __device__ int64_t group_start(Win& win, int64_t x) const
+// steps of one entry: the step it belongs to and its index in the step's line
+template <bool RAY>
+struct EntryKey {
+    int line;  // entry index = major line + minor
+    bool swap; // the step is the minor part
+    double inv;
+    __device__ __forceinline__ void operator()(int c, int* st, int* idx) const
     {
-        const int r = win.col(x) / N;
-        while (x > b && win.col(x - 1) / N == r) --x;
-        return x;
+        const int major = div_by(c, line, inv), minor = c - major * line;
+        *st = RAY && swap ? minor : major;
+        *idx = RAY && swap ? major : minor;
     }
-    template <typename Win>
-    __device__ RayWalk(Win& win, int n, int64_t b0, int64_t e0, bool reverse)
-        : N(n), b(b0), q(b0), gs(b0), ge(e0), rev(reverse && e0 > b0)
-    {
-        if (rev) q = gs = group_start(win, e0 - 1);
-    }
-    __device__ bool more() const { return q < ge; }
-    template <typename Win>
-    __device__ void next(Win& win)
-    {
-        if (++q == ge && rev && gs > b) {
-            ge = gs;
-            gs = group_start(win, gs - 1);
-            q = gs;
+};
+
+template <typename LenT>
+__device__ __forceinline__ void place(LayoutLds<LenT>& L, int x, int slot, int r, LenT l)
+{
+    const unsigned long long m0 = L.mask[0][x], m1 = L.mask[1][x], below = (1ull << r) - 1;
+    const int mine = slot ? (int)(m0 >> r & 1) : 0;  // b before b + 1
+    L.stage[L.off[x] + __popcll(m0 & below) + __popcll(m1 & below) + mine] = l;
+}
+
+// after the span's masks: its steps' places and heads; `total` lengths precede
+template <typename LenT>
+__device__ __forceinline__ void layout_places(LayoutLds<LenT>& L, StepHead* head, int x0, int steps, int total, int lane,
+                                              int w, int* first, int* last)
+{
+    constexpr int kSpan = LayoutLds<LenT>::kSpan;
+    if (w == 0) {
+        const int n = lane < kSpan ? __popcll(L.mask[0][lane]) + __popcll(L.mask[1][lane]) : 0;
+        const int pre = wave_excl_scan(n, lane);
+        if (lane < kSpan) {
+            L.off[lane] = pre;
+            if (x0 + lane < steps) head[x0 + lane] = StepHead{L.mask[0][lane], L.mask[1][lane], total + pre, 0};
+        }
+        if (lane == kSpan - 1) L.off[kSpan] = pre + n;
+        const unsigned long long some = __ballot(n > 0);
+        if (some) {
+            *first = min(*first, x0 + __ffsll((long long)some) - 1);
+            *last = max(*last, x0 + 63 - __clzll((long long)some));
         }
     }
-};
+    __syncthreads();
+}
 
-// One step of a tile build: each lane takes the entries of its row at step
-// st from its walk, and the wave writes the step's cells and base.  False
-// where the entries break the tile shape.  Every lane of the wavefront calls
-// it with the same st.
-template <typename LenT, typename Walk, typename Key>
-__device__ __forceinline__ bool tile_step(int st, int R, Walk& wk, EntryWindow<LenT>& win, const Key& key,
-                                          int64_t cell, int64_t bcell, uint8_t* __restrict__ off,
-                                          LenT* __restrict__ l0, LenT* __restrict__ l1,
-                                          int32_t* __restrict__ base)
+// one span of rays taken from the last step to the first.  (The next image
+// row's run ends at most one column right of where this one begins: once an
+// entry lies two columns left of the span, no later row reaches into it.)
+template <typename LenT>
+__device__ __forceinline__ void layout_span_down(LayoutLds<LenT>& L, const EntryKey<true>& key, int N, int K,
+                                                 const double* trig, int u, int k0, int x0, int x1, int now, int pass,
+                                                 int lane, int w, const int32_t* __restrict__ ci,
+                                                 const LenT* __restrict__ ln)
 {
-    int ia = -1, ib = -1;
-    LenT la = (LenT)0, lb = (LenT)0;
-    bool ok = true;
-    for (int c = 0; c < 3 && wk.more(); ++c) {
-        int s, idx;
-        key(win.col(wk.q), &s, &idx);
-        if (s != st) break;
-        if (c == 0) {
-            ia = idx;
-            la = win.len(wk.q);
-        } else if (c == 1) {
-            ib = idx;
-            lb = win.len(wk.q);
+#pragma unroll 1
+    for (int r = w * 16; r < w * 16 + 16; ++r) {
+        const int64_t b = L.row_b[r];
+        const int n = L.row_n[r];
+        const RayRow ray(N, K, trig, u, k0 + r);
+        int next = n;          // first entry left for later spans
+        int stop = INT32_MAX;  // the image row after which none reaches the span
+        for (int q0 = L.taken[now][r]; q0 < n; q0 += 64) {
+            const int q = q0 + lane;
+            const bool on = q < n;
+            const int c = ci[b + (on ? q : q0)];
+            const LenT l = ln[b + (on ? q : q0)];
+            int st, idx;
+            key(c, &st, &idx);
+            const bool in = on && st >= x0 && st < x1;
+            const int slot = idx - ray.at(trig, in ? st : x0);
+            if (in && slot != 0 && slot != 1) L.bad = 1;
+            if (in && (slot == 0 || slot == 1)) {
+                if (pass == 0)
+                    atomicOr(&L.mask[slot][st - x0], 1ull << r);
+                else
+                    place(L, st - x0, slot, r, l);
+            }
+            const unsigned long long later = __ballot(on && st < x0);
+            if (later && next == n) next = q0 + __ffsll((long long)later) - 1;
+            const unsigned long long past = __ballot(on && st < x0 - 1);
+            if (past && stop == INT32_MAX) stop = __builtin_amdgcn_readlane(idx, __ffsll((long long)past) - 1);
+            if (__ballot(on && idx > stop)) break;
+        }
+        if (pass == 0 && lane == 0) L.taken[now ^ 1][r] = next;
+    }
+}
+
+template <typename LenT, int MODE>
+__global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, int nkt, int64_t nnz,
+                                                         const double* __restrict__ trig,
+                                                         const int32_t* __restrict__ tiles,
+                                                         const int64_t* __restrict__ rp,
+                                                         const int32_t* __restrict__ ci,
+                                                         const LenT* __restrict__ ln,
+                                                         StepHead* __restrict__ heads, LenT* __restrict__ lens,
+                                                         int32_t* __restrict__ flag, bool force_csr)
+{
+    constexpr int kSpan = LayoutLds<LenT>::kSpan;
+    constexpr bool RAY = MODE != kPixels;
+    // rows of a wavefront; windows of 64 entries a span
+    constexpr int kRows = 16, kW = 2 * kSpan / 64 + (MODE == kRayDown ? 1 : 0);
+    __shared__ LayoutLds<LenT> L;
+    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int steps = RAY ? N : U;
+    const int u = RAY ? t / nkt : 0, k0 = RAY ? (t - u * nkt) * 64 : 0;
+    const bool cols = RAY && ray_cols(trig, u);
+    const bool falls = RAY && !cols && trig[2 * u] * trig[2 * u + 1] < 0.0;
+    constexpr bool down = MODE == kRayDown;
+    if (RAY && falls != down) return;  // the other kernel's tile
+    const bool flat = down && fabs(trig[2 * u + 1]) > 19.0 * fabs(trig[2 * u]);
+    const int line = RAY ? N : K;
+    const EntryKey<RAY> key{line, RAY && !cols, 1.0 / (double)line};
+    StepHead* head = heads + (int64_t)t * steps;
+    LenT* out = lens + (int64_t)t * steps * 128;
+    const int spans = (steps + kSpan - 1) / kSpan;
+    if (tid == 0) {
+        L.bad = force_csr ? 1 : 0;
+        L.entries = 0;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        int64_t row = -1;
+        if (RAY)
+            row = k0 + tid < K ? (int64_t)u * K + k0 + tid : -1;
+        else
+            row = tile_pixel(tiles, t, tid, N);
+        const int64_t b = row >= 0 ? rp[row] : 0;
+        const int n = row >= 0 ? (int)(rp[row + 1] - b) : 0;
+        L.row_b[tid] = n > 0 ? b : 0;
+        L.row_n[tid] = n;
+        L.taken[0][tid] = 0;
+        if (n > 0) atomicAdd(&L.entries, n);
+    }
+    int total = 0, first = steps, last = -1;
+    for (int sp = 0; sp < spans; ++sp) {
+        const int x0 = (down ? spans - 1 - sp : sp) * kSpan;
+        const int x1 = x0 + kSpan < steps ? x0 + kSpan : steps;
+        const int now = sp & 1;
+        if (tid < 2 * kSpan) L.mask[tid / kSpan][tid % kSpan] = 0;
+        __syncthreads();
+        if constexpr (down) {
+            if (flat) {
+                for (int pass = 0; pass < 2; ++pass) {
+                    layout_span_down<LenT>(L, key, N, K, trig, u, k0, x0, x1, now, pass, lane, w, ci, ln);
+                    __syncthreads();
+                    if (pass == 0) layout_places(L, head, x0, steps, total, lane, w, &first, &last);
+                }
+            }
+        }
+        if (!flat) {
+            int c[kRows][kW];  // entry indices, then step and slot
+            LenT l[kRows][kW];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int rr = w * kRows + r;
+                const int64_t b = lane0_i64(L.row_b[rr]);
+                const int n = __builtin_amdgcn_readfirstlane(L.row_n[rr]);
+                const int from = __builtin_amdgcn_readfirstlane(L.taken[now][rr]);
+#pragma unroll
+                for (int h = 0; h < kW; ++h) {
+                    const int q = from + 64 * h + lane;
+                    const uint32_t at = q < n ? (uint32_t)q : 0u;  // (an empty row: the array's first entry)
+                    c[r][h] = nnz > 0 ? ci[b + at] : 0;
+                    l[r][h] = nnz > 0 ? ln[b + at] : (LenT)0.0;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int rr = w * kRows + r;
+                const int n = __builtin_amdgcn_readfirstlane(L.row_n[rr]);
+                const int from = __builtin_amdgcn_readfirstlane(L.taken[now][rr]);
+                const RayRow ray(N, K, trig, u, k0 + rr);
+                const PixelRow px(N, K, RAY ? 0 : tile_pixel(tiles, t, rr, N));
+                const int past = min(n, from + 64 * kW);
+                int next = past;  // first entry left for later spans
+#pragma unroll
+                for (int h = 0; h < kW; ++h) {
+                    int st, idx;
+                    key(c[r][h], &st, &idx);
+                    const bool on = from + 64 * h + lane < n;
+                    const bool in = on && st >= x0 && st < x1;
+                    const int slot = idx - (RAY ? ray.at(trig, in ? st : x0) : px.at(trig, in ? st : x0));
+                    const bool ok = slot == 0 || slot == 1;
+                    if (in && !ok) L.bad = 1;
+                    if (in && ok) atomicOr(&L.mask[slot][st - x0], 1ull << rr);
+                    c[r][h] = in && ok ? (st - x0) * 2 + slot : -1;
+                    const unsigned long long later = __ballot(on && (down ? st < x0 : st >= x1));
+                    if (later && next == past) next = from + 64 * h + __ffsll((long long)later) - 1;
+                }
+                if (lane == 0) L.taken[now ^ 1][rr] = next;
+            }
+            __syncthreads();
+            layout_places(L, head, x0, steps, total, lane, w, &first, &last);
+#pragma unroll
+            for (int r = 0; r < kRows; ++r)
+#pragma unroll
+                for (int h = 0; h < kW; ++h)
+                    if (c[r][h] >= 0) place(L, c[r][h] >> 1, c[r][h] & 1, w * kRows + r, l[r][h]);
+            __syncthreads();
+        }
+        const int n = L.off[kSpan];
+        for (int q = tid; q < n; q += 256) out[total + q] = L.stage[q];
+        total += n;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const bool odd = L.bad || total != L.entries;
+        if (RAY) {
+            flag[2 * t] = odd ? 0 : first;
+            flag[2 * t + 1] = odd ? kOdd : last;
         } else {
-            ok = false;
+            flag[t] = odd ? kOdd : 0;
         }
-        wk.next(win);
     }
-    if (ib >= 0 && ib < ia) {
-        const int ti = ia;
-        ia = ib;
-        ib = ti;
-        const LenT tl = la;
-        la = lb;
-        lb = tl;
-    }
-    if (ib >= 0 && ib != ia + 1) ok = false;
-    if (ia >= R || (ia < 0 && ib >= 0)) {  // not an index of this step's line
-        ok = false;
-        ia = ib = -1;
-    }
-    int m = ia >= 0 ? ia : INT_MAX;
-    for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, 64));
-    const int d = ia >= 0 ? ia - m : 0;
-    if (d > 255) ok = false;
-    off[cell] = (uint8_t)(d > 255 ? 0 : d);
-    l0[cell] = la;
-    l1[cell] = lb;
-    if ((threadIdx.x & 63) == 0) base[bcell] = m == INT_MAX ? 0 : m;
-    return ok;
 }
 
-// Sum over the steps lo..hi of one lane's tile cells: l0 src[s R + x] +
-// l1 src[s R + x + 1] with x = base[s] + offset, S steps at a time.  The
-// next group's cells are loaded after this group's gathers are issued, so
-// they are in flight while the gathers are waited for (loads complete in
-// issue order).  Terms are added by ascending step, l0 before l1.
-template <typename LenT, int S>
-__device__ __forceinline__ double tile_sum(int lo, int hi, int R, const int32_t* __restrict__ tb,
-                                           const uint8_t* __restrict__ off, const LenT* __restrict__ l0,
-                                           const LenT* __restrict__ l1, int64_t cb,
-                                           const double* __restrict__ src)
+// two neighbouring values in one load (aligned as one value is)
+template <typename T>
+struct Pair {
+    T x, y;
+};
+template <typename T>
+__device__ __forceinline__ Pair<T> pair_at(const T* base, uint32_t i)
 {
-    double acc = 0.0;
-    if (lo > hi) return acc;
-    int32_t ii[S];
-    LenT a0[S], a1[S];
-    auto load = [&](int s0) {
+    Pair<T> p;
+    __builtin_memcpy(&p, (const char*)base + i * (uint32_t)sizeof(T), sizeof(p));
+    return p;
+}
+
+// The S steps from s0: their heads (uniform) first, then lengths and values
+// of all of them in flight at once, one load for a lane's two lengths (which
+// are neighbours) and one for its two values; absent entries are left out of
+// the sum (not added as zeros: what is read in their place may be anything).
+// A line has at least two values.
+template <typename LenT, int S, typename Row>
+__device__ __forceinline__ double tile_steps(double acc, int s0, int line, const Row& row,
+                                             const double* __restrict__ trig, const StepHead* __restrict__ head,
+                                             const LenT* __restrict__ lens, const double* __restrict__ src)
+{
+    uint64_t m0[S], m1[S];
+    uint32_t pos[S];
+    int b[S], at[S];
 #pragma unroll
-        for (int a = 0; a < S; ++a) {
-            const int st = s0 + a <= hi ? s0 + a : hi;
-            ii[a] = tb[st] + (int32_t)off[cb + (int64_t)st * 64];
-            a0[a] = l0[cb + (int64_t)st * 64];
-            a1[a] = l1[cb + (int64_t)st * 64];
-        }
-    };
-    load(lo);
-    for (int s0 = lo; s0 <= hi; s0 += S) {
-        double v0[S], v1[S];
-        LenT c0[S], c1[S];
+    for (int a = 0; a < S; ++a) {
+        m0[a] = head[s0 + a].m0;
+        m1[a] = head[s0 + a].m1;
+        pos[a] = (uint32_t)head[s0 + a].pos;
+    }
 #pragma unroll
-        for (int a = 0; a < S; ++a) {
-            const int st = s0 + a <= hi ? s0 + a : hi;
-            const int64_t at = (int64_t)st * R + ii[a];
-            v0[a] = src[at];
-            v1[a] = src[ii[a] + 1 < R ? at + 1 : at];
-            c0[a] = a0[a];
-            c1[a] = a1[a];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (s0 + S <= hi) load(s0 + S);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int a = 0; a < S; ++a) {
+        b[a] = row.at(trig, s0 + a);
+        at[a] = min(max(b[a], 0), line - 2);
+    }
+    Pair<double> v[S];
+    Pair<LenT> l[S];
 #pragma unroll
-        for (int a = 0; a < S; ++a) {
-            if (s0 + a <= hi) {
-                acc = fma((double)c0[a], v0[a], acc);
-                acc = fma((double)c1[a], v1[a], acc);
-            }
-        }
+    for (int a = 0; a < S; ++a) {
+        uint32_t i = __builtin_amdgcn_mbcnt_lo((uint32_t)m0[a], pos[a]);
+        i = __builtin_amdgcn_mbcnt_hi((uint32_t)(m0[a] >> 32), i);
+        i = __builtin_amdgcn_mbcnt_lo((uint32_t)m1[a], i);
+        i = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1[a] >> 32), i);
+        l[a] = pair_at(lens, i);
+        v[a] = pair_at(src + (int64_t)(s0 + a) * line, (uint32_t)at[a]);
+    }
+#pragma unroll
+    for (int a = 0; a < S; ++a) {
+        const bool h0 = __builtin_amdgcn_inverse_ballot_w64(m0[a]), h1 = __builtin_amdgcn_inverse_ballot_w64(m1[a]);
+        const bool in = b[a] == at[a];  // else b + 1 is the line's first value, or b its last
+        const double x = fma((double)l[a].x, in ? v[a].x : v[a].y, acc);
+        acc = h0 ? x : acc;
+        const double y = fma((double)(h0 ? l[a].y : l[a].x), in ? v[a].y : v[a].x, acc);
+        acc = h1 ? y : acc;
     }
     return acc;
 }
 
-template <typename LenT>
-__global__ __launch_bounds__(64) void tile_build_kernel(int N, int U, int K, const int32_t* __restrict__ tiles,
-                                                       const int64_t* __restrict__ rp,
-                                                       const int32_t* __restrict__ ci,
-                                                       const LenT* __restrict__ ln,
-                                                       uint8_t* __restrict__ off, LenT* __restrict__ l0,
-                                                       LenT* __restrict__ l1, int32_t* __restrict__ base,
-                                                       int32_t* __restrict__ flag, int64_t nnz, bool vec,
-                                                       bool force_csr)
+// Sum over the steps lo..hi of one lane's entries: length times src[step line
+// + b (+ 1)], by ascending step, b before b + 1.
+template <typename LenT, int S, typename Row>
+__device__ __forceinline__ double tile_sum(int lo, int hi, int line, const Row& row, const double* __restrict__ trig,
+                                           const StepHead* __restrict__ head, const LenT* __restrict__ lens,
+                                           const double* __restrict__ src)
 {
-    __shared__ WindowLds<LenT> lds;
-    const int t = blockIdx.x, lane = threadIdx.x;
-    const int64_t p = tile_pixel(tiles, t, lane, N);
-    auto key = [&](int g, int* s, int* idx) {
-        const int u = g / K;
-        *s = u;
-        *idx = g - u * K;
-    };
-    EntryWindow<LenT> win = entry_window(lds, lane, ci, ln, nnz, vec);
-    RowWalk wk{p >= 0 ? rp[p] : 0, p >= 0 ? rp[p + 1] : 0};
-    bool ok = true;
-    for (int u = 0; u < U; ++u) {
-        const int64_t bc = (int64_t)t * U + u;
-        ok &= tile_step<LenT>(u, K, wk, win, key, bc * 64 + lane, bc, off, l0, l1, base);
-    }
-    if (wk.more() || force_csr) ok = false;
-    const bool odd = __any(!ok);
-    if (lane == 0) flag[t] = odd ? kOdd : 0;
+    double acc = 0.0;
+    int s = lo;
+    for (; s + S - 1 <= hi; s += S) acc = tile_steps<LenT, S>(acc, s, line, row, trig, head, lens, src);
+    for (; s <= hi; ++s) acc = tile_steps<LenT, 1>(acc, s, line, row, trig, head, lens, src);
+    return acc;
 }
 
 // Workgroup b's tile: workgroups go to the 8 XCDs round robin, so XCD x
@@ -479,24 +613,33 @@ __device__ __forceinline__ void wave_part(int lo, int hi, int w, int* a, int* b)
 }
 
 // One workgroup per pixel tile; its 4 wavefronts take a quarter of the
-// angles each, and their sums are added in wavefront order.
+// angles each, and their sums are added in wavefront order.  The new values
+// go to the image and to its transpose, which the next iteration's projection
+// reads; the workgroup after the last tile adds up the iteration's squared
+// residuals.  (Both took a kernel of their own, 5 us each at 256 x 256 where
+// this one takes 22.)
 template <typename LenT>
 __global__ __launch_bounds__(256) void tile_back_kernel(int N, int U, int K, int n_tiles,
+                                                       const double* __restrict__ trig,
                                                        const int32_t* __restrict__ tiles,
                                                        const int64_t* __restrict__ rp,
                                                        const int32_t* __restrict__ ci,
                                                        const LenT* __restrict__ ln,
                                                        const int32_t* __restrict__ flag,
-                                                       const uint8_t* __restrict__ off,
-                                                       const LenT* __restrict__ l0,
-                                                       const LenT* __restrict__ l1,
-                                                       const int32_t* __restrict__ base,
+                                                       const StepHead* __restrict__ heads,
+                                                       const LenT* __restrict__ lens,
                                                        const double* __restrict__ y,
-                                                       double* __restrict__ f, double scale)
+                                                       double* __restrict__ f, double* __restrict__ fT, double scale,
+                                                       const double* __restrict__ partial, int n_partial,
+                                                       double* __restrict__ sse)
 {
     constexpr int kA = 8;  // angles in flight
+    if (blockIdx.x == gridDim.x - 1) {
+        sum_partials(partial, n_partial, sse);
+        return;
+    }
     __shared__ double part[kWPB][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = xcd_tile(n_tiles);
     if (t < 0) return;
     const int64_t p = tile_pixel(tiles, (int)t, lane, N);
@@ -507,68 +650,18 @@ __global__ __launch_bounds__(256) void tile_back_kernel(int N, int U, int K, int
     } else {
         int a, b;
         wave_part(0, U - 1, w, &a, &b);
-        acc = tile_sum<LenT, kA>(a, b, K, base + t * U, off, l0, l1, t * U * 64 + lane, y);
+        const PixelRow row(N, K, p);
+        acc = tile_sum<LenT, kA>(a, b, K, row, trig, heads + t * U, lens + t * U * 128, y);
     }
     part[w][lane] = acc;
     __syncthreads();
     if (w == 0) {
         const double sum = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-        if (p >= 0 && rp[p + 1] > rp[p]) f[p] = f[p] + scale * sum;
-    }
-}
-
-template <typename LenT>
-__global__ __launch_bounds__(64) void ray_tile_build_kernel(int N, int U, int K, int nkt,
-                                                           const double* __restrict__ trig,
-                                                           const int64_t* __restrict__ rp,
-                                                           const int32_t* __restrict__ ci,
-                                                           const LenT* __restrict__ ln,
-                                                           uint8_t* __restrict__ off, LenT* __restrict__ l0,
-                                                           LenT* __restrict__ l1, int32_t* __restrict__ base,
-                                                           int32_t* __restrict__ range, int64_t nnz, bool vec,
-                                                           bool force_csr)
-{
-    __shared__ WindowLds<LenT> lds;
-    const int t = blockIdx.x, lane = threadIdx.x;
-    const int u = t / nkt, k = (t - u * nkt) * 64 + lane;
-    const bool cols = ray_cols(trig, u);
-    auto key = [&](int p, int* s, int* idx) {
-        const int i = p / N, j = p - i * N;
-        *s = cols ? i : j;
-        *idx = cols ? j : i;
-    };
-    EntryWindow<LenT> win = entry_window(lds, lane, ci, ln, nnz, vec);
-    const int64_t g = (int64_t)u * K + k;
-    const int64_t b = k < K ? rp[g] : 0, e = k < K ? rp[g + 1] : 0;
-    int lo = N, hi = -1;
-    bool bad = false;
-    for (int64_t q = b; q < e; ++q) {
-        int s, x;
-        key(win.col(q), &s, &x);
-        if (s < 0 || s >= N) {  // not a pixel index: the tile is summed from the CSR
-            bad = true;
-            continue;
+        if (p >= 0 && rp[p + 1] > rp[p]) {
+            const double v = f[p] + scale * sum;
+            f[p] = v;
+            fT[(p % N) * N + p / N] = v;
         }
-        lo = min(lo, s);
-        hi = max(hi, s);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o, 64));
-        hi = max(hi, __shfl_xor(hi, o, 64));
-    }
-    // a row of the image is one pixel high, and the ray moves s / c pixels
-    // along it per row: its columns fall as its rows rise where c s < 0
-    RayWalk wk(win, N, b, e, !cols && trig[2 * u] * trig[2 * u + 1] < 0.0);
-    bool ok = true;
-    for (int st = lo; st <= hi; ++st) {
-        const int64_t bc = (int64_t)t * N + st;
-        ok &= tile_step<LenT>(st, N, wk, win, key, bc * 64 + lane, bc, off, l0, l1, base);
-    }
-    if (wk.more() || bad || force_csr) ok = false;
-    const bool odd = __any(!ok);
-    if (lane == 0) {
-        range[2 * t] = odd ? 0 : lo;
-        range[2 * t + 1] = odd ? kOdd : hi;
     }
 }
 
@@ -577,20 +670,25 @@ __global__ __launch_bounds__(64) void ray_tile_build_kernel(int N, int U, int K,
 // a megabyte, and the work items (tile, band) of an XCD run band by band, so
 // that the XCD's L2 holds the image lines its gathers need.  An item writes
 // its 64 partial sums; ray_tile_res_kernel adds them in band order.
-int ray_band(int N)
+//
+// A band also is a wavefront's share of a tile: where the tiles are few (n_rt
+// of them) the bands are cut further, to 8 steps at the least, for some 8000
+// wavefronts (256 x 256, 180 angles, FP64, where 1080 tiles are one wavefront
+// a SIMD: 59 -> 23 us).
+int ray_band(int N, int64_t n_rt)
 {
-    int b = 131072 / (N > 0 ? N : 1);
+    int64_t b = 131072 / (N > 0 ? N : 1);
     b = b < 8 ? 8 : (b > 256 ? 256 : b);
-    return b & ~7;
+    const int64_t few = (int64_t)N * n_rt / 8192;
+    b = b < few ? b : few;
+    return b < 8 ? 8 : (int)(b & ~(int64_t)7);
 }
 
 template <typename LenT>
 __global__ __launch_bounds__(64) void ray_tile_part_kernel(int N, int K, int nkt, int n_tiles, int band,
                                                            int n_bands, const double* __restrict__ trig,
-                                                           const uint8_t* __restrict__ off,
-                                                           const LenT* __restrict__ l0,
-                                                           const LenT* __restrict__ l1,
-                                                           const int32_t* __restrict__ base,
+                                                           const StepHead* __restrict__ heads,
+                                                           const LenT* __restrict__ lens,
                                                            const int32_t* __restrict__ range,
                                                            const int64_t* __restrict__ rp,
                                                            const int32_t* __restrict__ ci,
@@ -618,7 +716,8 @@ __global__ __launch_bounds__(64) void ray_tile_part_kernel(int N, int K, int nkt
     } else {
         const int b0 = (int)bnd * band;
         const int a = lo > b0 ? lo : b0, b = hi < b0 + band - 1 ? hi : b0 + band - 1;
-        acc = tile_sum<LenT, kS>(a, b, N, base + t * N, off, l0, l1, t * N * 64 + lane, img);
+        const RayRow row(N, K, trig, u, k);
+        acc = tile_sum<LenT, kS>(a, b, N, row, trig, heads + t * N, lens + t * N * 128, img);
     }
     part[(bnd * n_tiles + t) * 64 + lane] = acc;
 }
@@ -671,14 +770,14 @@ std::vector<int32_t> support_tiles(const pila_geom* g)
 // SIRT workspace: factor matrix, scaled residual, block partials, costs,
 // the transposed image and the tile layout
 struct SirtLayout {
-    size_t W, q, partial, sse, fT, tiles, flag, off, l0, l1, base, roff, r0, r1, rbase, range, bpart, total;
+    size_t W, q, partial, sse, fT, tiles, flag, heads, lens, rheads, rlens, range, bpart, total;
 };
 
 SirtLayout sirt_layout(const pila_geom* g, int32_t n_iter, size_t n_tiles)
 {
     const size_t G = (size_t)g->n_angles * g->n_bins, NP = (size_t)g->n * g->n;
     const size_t ls = (size_t)len_bytes(g->len_dtype);
-    const size_t cells = n_tiles * (size_t)g->n_angles * 64;
+    const size_t cells = n_tiles * (size_t)g->n_angles;
     SirtLayout L;
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -693,18 +792,14 @@ SirtLayout sirt_layout(const pila_geom* g, int32_t n_iter, size_t n_tiles)
     L.fT = take(sizeof(double) * NP);
     L.tiles = take(sizeof(int32_t) * (n_tiles ? n_tiles : 1));
     L.flag = take(sizeof(int32_t) * (n_tiles ? n_tiles : 1));
-    L.off = take(cells);
-    L.l0 = take(ls * cells);
-    L.l1 = take(ls * cells);
-    L.base = take(sizeof(int32_t) * (cells / 64));
+    L.heads = take(sizeof(StepHead) * cells);
+    L.lens = take(ls * 128 * cells);  // at most two lengths per lane and step
     const size_t nrt = (size_t)g->n_angles * ((g->n_bins + 63) / 64);
-    const size_t rcells = nrt * (size_t)g->n * 64;
-    L.roff = take(rcells);
-    L.r0 = take(ls * rcells);
-    L.r1 = take(ls * rcells);
-    L.rbase = take(sizeof(int32_t) * (rcells / 64));
+    const size_t rcells = nrt * (size_t)g->n;
+    L.rheads = take(sizeof(StepHead) * rcells);
+    L.rlens = take(ls * 128 * rcells);
     L.range = take(sizeof(int32_t) * 2 * nrt);
-    const int band = ray_band(g->n);
+    const int band = ray_band(g->n, (int64_t)nrt);
     const size_t n_bands = (size_t)((g->n + band - 1) / band);
     L.bpart = take(sizeof(double) * n_bands * nrt * 64);
     // last, so that the layouts above sit at the same offsets for any n_iter
@@ -788,11 +883,6 @@ extern "C" int32_t sirt_workspace_size(const pila_geom* geom, const sirt_params*
     return PILA_OK;
 }
 
-static bool aligned16(const void* a, const void* b)
-{
-    return ((uintptr_t)a % 16) == 0 && ((uintptr_t)b % 16) == 0;
-}
-
 template <typename LenT>
 static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const double* d_sino,
                          const sirt_params* prm, double* d_image, char* ws, double* h_cost,
@@ -810,14 +900,12 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     double* fT = (double*)(ws + L.fT);
     int32_t* d_tiles = (int32_t*)(ws + L.tiles);
     int32_t* flag = (int32_t*)(ws + L.flag);
-    uint8_t* off = (uint8_t*)(ws + L.off);
-    LenT* l0 = (LenT*)(ws + L.l0);
-    LenT* l1 = (LenT*)(ws + L.l1);
-    int32_t* base = (int32_t*)(ws + L.base);
+    StepHead* heads = (StepHead*)(ws + L.heads);
+    LenT* lens = (LenT*)(ws + L.lens);
     // PILA_SIRT_CSR=1 sums every tile from its CSR rows (the path a tile of
     // irregular shape takes), for tests of that path
     const char* env = std::getenv("PILA_SIRT_CSR");
-    const bool force_csr = env && env[0] == '1';
+    const bool force_csr = (env && env[0] == '1') || N < 2 || K < 2;  // (a line of one value: from the rows too)
     const bool reuse = (prm->flags & PILA_SIRT_REUSE_LAYOUT) != 0;
     // factor matrix: W_g = sum of squared lengths of ray g over the support
     if (!reuse)
@@ -825,37 +913,37 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     if (n_tiles > 0 && !reuse) {
         PILA_HIP(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int32_t) * tiles.size(),
                                 hipMemcpyHostToDevice, st));
-        tile_build_kernel<LenT><<<n_tiles, 64, 0, st>>>(N, U, K, d_tiles, csr->row_ptr, csr->col,
-                                                        (const LenT*)csr->len, off, l0, l1, base, flag,
-                                                        csr->nnz, aligned16(csr->col, csr->len), force_csr);
+        tile_layout_kernel<LenT, kPixels><<<n_tiles, 256, 0, st>>>(N, U, K, 0, csr->nnz, csr->trig, d_tiles, csr->row_ptr,
+                                                                 csr->col, (const LenT*)csr->len, heads, lens, flag,
+                                                                 force_csr);
     }
     const int nkt = (K + 63) / 64, n_rt = U * nkt;
-    uint8_t* roff = (uint8_t*)(ws + L.roff);
-    LenT* r0 = (LenT*)(ws + L.r0);
-    LenT* r1 = (LenT*)(ws + L.r1);
-    int32_t* rbase = (int32_t*)(ws + L.rbase);
+    StepHead* rheads = (StepHead*)(ws + L.rheads);
+    LenT* rlens = (LenT*)(ws + L.rlens);
     int32_t* range = (int32_t*)(ws + L.range);
     double* bpart = (double*)(ws + L.bpart);
-    const int band = ray_band(N), n_bands = (N + band - 1) / band;
-    if (!reuse)
-        ray_tile_build_kernel<LenT><<<n_rt, 64, 0, st>>>(N, U, K, nkt, csr->trig, csr->t_row_ptr, csr->t_col,
-                                                         (const LenT*)csr->t_len, roff, r0, r1, rbase, range,
-                                                         csr->nnz, aligned16(csr->t_col, csr->t_len), force_csr);
+    const int band = ray_band(N, n_rt), n_bands = (N + band - 1) / band;
+    if (!reuse) {
+        tile_layout_kernel<LenT, kRayUp><<<n_rt, 256, 0, st>>>(N, U, K, nkt, csr->nnz, csr->trig, nullptr,
+                                                              csr->t_row_ptr, csr->t_col, (const LenT*)csr->t_len,
+                                                              rheads, rlens, range, force_csr);
+        tile_layout_kernel<LenT, kRayDown><<<n_rt, 256, 0, st>>>(N, U, K, nkt, csr->nnz, csr->trig, nullptr,
+                                                                csr->t_row_ptr, csr->t_col, (const LenT*)csr->t_len,
+                                                                rheads, rlens, range, force_csr);
+    }
 
     const double scale = prm->lambda / (double)geom->n_angles;
     const dim3 tgrid((unsigned)((N + 31) / 32), (unsigned)((N + 31) / 32));
+    if (prm->n_iter > 0) transpose_kernel<<<tgrid, 256, 0, st>>>(N, d_image, fT);
     for (int32_t it = 0; it < prm->n_iter; ++it) {
-        transpose_kernel<<<tgrid, 256, 0, st>>>(N, d_image, fT);
         ray_tile_part_kernel<LenT><<<(unsigned)(8 * ((n_rt + 7) / 8) * n_bands), 64, 0, st>>>(
-            N, K, nkt, n_rt, band, n_bands, csr->trig, roff, r0, r1, rbase, range, csr->t_row_ptr, csr->t_col,
+            N, K, nkt, n_rt, band, n_bands, csr->trig, rheads, rlens, range, csr->t_row_ptr, csr->t_col,
             (const LenT*)csr->t_len, d_image, fT, bpart);
         ray_tile_res_kernel<<<(unsigned)((n_rt + kWPB - 1) / kWPB), 256, 0, st>>>(K, nkt, n_rt, n_bands, bpart,
                                                                                 d_sino, W, q, partial);
-        reduce_kernel<<<1, 256, 0, st>>>(partial, n_rt, sse + it);
-        if (n_tiles > 0)
-            tile_back_kernel<LenT><<<xcd_grid(n_tiles), 256, 0, st>>>(
-                N, U, K, n_tiles, d_tiles, csr->row_ptr, csr->col, (const LenT*)csr->len, flag, off, l0, l1,
-                base, q, d_image, scale);
+        tile_back_kernel<LenT><<<xcd_grid(n_tiles) + 1, 256, 0, st>>>(
+            N, U, K, n_tiles, csr->trig, d_tiles, csr->row_ptr, csr->col, (const LenT*)csr->len, flag, heads, lens, q,
+            d_image, fT, scale, partial, n_rt, sse + it);
     }
     PILA_HIP(hipGetLastError());
     if (h_cost && prm->n_iter > 0) {
