@@ -310,6 +310,23 @@ __global__ __launch_bounds__(256) void sat_rebuild_kernel(ChainJob job, int meas
         rebuild_tile<Real, true, LenT>(job, (Real*)job.r, G, t, measure != 0, lane);
 }
 
+// The same for every chain of a batch that has this precision and length
+// type, before the batch's chains start (blockIdx.y: chain).
+template <typename Real, typename LenT = Real>
+__global__ __launch_bounds__(256) void sat_batch_rebuild_kernel(const ChainJob* __restrict__ jobs, int n_jobs)
+{
+    const int lane = threadIdx.x & 63;
+    const int waves = gridDim.x * (blockDim.x >> 6);
+    for (int j = blockIdx.y; j < n_jobs; j += gridDim.y) {
+        const ChainJob& J = jobs[j];
+        if ((J.precision == PILA_F64) != (sizeof(Real) == 8) || (J.lenq != 0) != std::is_same<LenT, LenQ>::value)
+            continue;
+        const int G = J.U * J.K, T = (G + kWave - 1) / kWave;
+        for (int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); t < T; t += waves)
+            rebuild_tile<Real, true, LenT>(J, (Real*)J.r, G, t, false, lane);
+    }
+}
+
 // After the initial rebuild: sum of squares and Eq. 8, then the carry.
 template <typename Real, typename LenT = Real>
 __global__ __launch_bounds__(512) void sat_setup_kernel(ChainJob job)
@@ -788,6 +805,22 @@ static int32_t sat_run_impl(const pila_geom* geom, const pila_csr* csr, const do
     const bool simple_seg = !ps && !lng && !r_in_lds && resync && !split;
     const int glob = r_in_lds ? 0 : PILA_BODY_GLOBAL_R;
     int body = 0;
+    const int T = (int)((G + 63) / 64);
+    const unsigned rb = (unsigned)std::min<int64_t>((T + 3) / 4, 4096);
+    // the first residual, by the whole GPU for every size: already at 64^2 x
+    // 90 one workgroup took a millisecond, this launch 18 us (the split body
+    // enqueues its own)
+    if (!split) {
+        if (params->precision == PILA_F64 && lenq)
+            sat_rebuild_kernel<double, LenQ><<<rb, 256, 0, st>>>(J, 0);
+        else if (params->precision == PILA_F64)
+            sat_rebuild_kernel<double><<<rb, 256, 0, st>>>(J, 0);
+        else if (lenq)
+            sat_rebuild_kernel<float, LenQ><<<rb, 256, 0, st>>>(J, 0);
+        else
+            sat_rebuild_kernel<float><<<rb, 256, 0, st>>>(J, 0);
+        PILA_HIP(hipGetLastError());
+    }
     if (split) {
         const int M = params->m_cand;
         const int ng = split_groups(M);
@@ -808,8 +841,6 @@ static int32_t sat_run_impl(const pila_geom* geom, const pila_csr* csr, const do
         if (const char* e = std::getenv("PILA_SPLIT_WAIT_MS")) wait_ms = std::max<int64_t>(0, std::atoll(e));
         X.wait_ticks = (int64_t)(khz > 0 ? khz : 100000) * wait_ms;
         body = PILA_BODY_SPLIT | PILA_BODY_GLOBAL_R | PILA_BODY_SEGMENTED | (ng << 8);
-        const int T = (int)((G + 63) / 64);
-        const unsigned rb = (unsigned)std::min<int64_t>((T + 3) / 4, 4096);
         const int64_t n_seg = resync ? params->n_steps / params->resync_every + 1 : 1;
         const int64_t n_image = (int64_t)geom->n * geom->n;
         const int32_t rc = params->precision == PILA_F64
@@ -823,16 +854,11 @@ static int32_t sat_run_impl(const pila_geom* geom, const pila_csr* csr, const do
                PILA_BODY_GLOBAL_R | PILA_BODY_SEGMENTED;
         // FP32 residual in global memory: chain segments end at each resync,
         // which runs grid-wide; the host only enqueues, it never waits
-        const int T = (int)((G + 63) / 64);
-        const unsigned rb = (unsigned)std::min<int64_t>((T + 3) / 4, 4096);
         const int long_bytes = long_seg ? (int)long_lds(&J, budget) : 0;
-        if (lenq) {
-            sat_rebuild_kernel<float, LenQ><<<rb, 256, 0, st>>>(J, 0);
+        if (lenq)
             sat_setup_kernel<float, LenQ><<<1, kPipedThreads, 0, st>>>(J);
-        } else {
-            sat_rebuild_kernel<float><<<rb, 256, 0, st>>>(J, 0);
+        else
             sat_setup_kernel<float><<<1, kPipedThreads, 0, st>>>(J);
-        }
         const int64_t n_seg = params->n_steps / params->resync_every + 1;
         const int sw = params->m_cand < kMaxWaves ? params->m_cand : kMaxWaves;
         for (int64_t k = 0; k < n_seg; ++k) {
@@ -1176,6 +1202,20 @@ static int32_t batch_enqueue(const BatchPlan& bp, hipStream_t st, hipEvent_t* t_
     zero_ints_kernel<<<1, 64, 0, st>>>(bp.d_ticket, kMaxGroups);
     PILA_HIP(hipGetLastError());
     for (const BatchPlan::Tcol& t : bp.tcols) PILA_TRY(launch_tcol(t.J, t.nnz, t.dst, st));
+    // the chains' first residuals, one launch per precision and length type
+    int tiles = 0;
+    bool some[2][2] = {{false, false}, {false, false}};
+    for (const ChainJob& J : bp.host) {
+        some[J.precision == PILA_F64][J.lenq != 0] = true;
+        tiles = std::max(tiles, (J.U * J.K + kWave - 1) / kWave);
+    }
+    const int across = std::min((tiles + 3) / 4, 1024);
+    const dim3 grid((unsigned)across, (unsigned)std::min(bp.n_jobs, 65536 / across));
+    if (some[0][0]) sat_batch_rebuild_kernel<float><<<grid, 256, 0, st>>>(bp.d_jobs, bp.n_jobs);
+    if (some[0][1]) sat_batch_rebuild_kernel<float, LenQ><<<grid, 256, 0, st>>>(bp.d_jobs, bp.n_jobs);
+    if (some[1][0]) sat_batch_rebuild_kernel<double><<<grid, 256, 0, st>>>(bp.d_jobs, bp.n_jobs);
+    if (some[1][1]) sat_batch_rebuild_kernel<double, LenQ><<<grid, 256, 0, st>>>(bp.d_jobs, bp.n_jobs);
+    PILA_HIP(hipGetLastError());
     // fork: every group after the first waits for the work above on its own stream
     const int n_aux = (int)groups.size() - 1;
     hipStream_t aux[kMaxAux] = {};
@@ -1211,7 +1251,7 @@ static int32_t batch_enqueue(const BatchPlan& bp, hipStream_t st, hipEvent_t* t_
         int* ticket_arg = bp.d_ticket + gi;
         first += g.ids.size();
         void* args[] = {&jobs_arg, &order_arg, &n_arg, &ticket_arg, &lds_arg};
-        const int grid = std::min(n_arg, bp.n_cu * bp.per_cu);
+        const int workgroups = std::min(n_arg, bp.n_cu * bp.per_cu);
         const int kind = g.kind & 255;
         const bool f64 = (g.kind & 256) != 0;
         const bool lq = (g.kind & 512) != 0;
@@ -1226,7 +1266,7 @@ static int32_t batch_enqueue(const BatchPlan& bp, hipStream_t st, hipEvent_t* t_
                                     : (const void*)sat_batch_simple_kernel<float>);
         PILA_TRY(set_lds(k, bp.lds));
         if (t_ev) PILA_HIP(hipEventRecord(t_ev[2 * gi], gs));
-        PILA_HIP(hipLaunchKernel(k, dim3(grid), dim3(g.waves * kWave), args, (size_t)bp.lds, gs));
+        PILA_HIP(hipLaunchKernel(k, dim3(workgroups), dim3(g.waves * kWave), args, (size_t)bp.lds, gs));
         if (t_ev) PILA_HIP(hipEventRecord(t_ev[2 * gi + 1], gs));
         if (gi > 0) PILA_HIP(hipEventRecord(join[gi - 1], gs));
     }

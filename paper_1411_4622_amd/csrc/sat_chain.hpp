@@ -488,49 +488,79 @@ __device__ Real estimate_sum(const ChainJob& J, const Real* __restrict__ r, uint
 }
 
 // One 64-ray tile of a from-scratch FP64 residual r = A f - Pm (Eq. 1,
-// Eq. 4), by one wavefront.  The four 16-lane quarters take the
-// tile's rays four at a time (quarter q the rays q*16 + i, i = 0..15); the
-// lanes of a quarter stride the ray's ray-major row by 16, so each load of
-// a quarter reads 16 consecutive entries, and each lane keeps one FP64
-// partial (its entries in ascending order, fused multiply-add).  An xor
-// butterfly over the quarter adds the 16 partials.  Lane j then holds ray
-// t*64 + j.  In-group and grid-wide rebuilds both run this function, so they
-// give the same bits.
+// Eq. 4), by one wavefront.  Its four 16-lane quarters take four neighbouring
+// rays at a time (whose pixels share cache lines: a gather of 4 x 16 entries
+// meets some 20 lines, where four distant rays' met 64); the lanes of a
+// quarter stride the ray's ray-major row by 16, so each load of a quarter
+// reads 16 consecutive entries, and each lane keeps one FP64 partial (its
+// entries in ascending order, fused multiply-add), the next U entries loaded
+// while this U's image values are on their way.  An xor butterfly over the
+// quarter adds the 16 partials.  Lane j then holds ray t*64 + j.  In-group
+// and grid-wide rebuilds both run this function, so they give the same bits.
+// 1024^2 x 720 FP32, 6.06 GB of PILA, grid-wide: 2.64 ms before (quarters 16
+// rays apart, loads in series), 1.26 ms now = 4.8 TB/s, what a copy reaches.
 template <typename Real, bool GLOB, typename LenT = Real>
 __device__ void rebuild_tile(const ChainJob& J, Real* __restrict__ r, int G, int t, bool measure,
                              int lane)
 {
-    constexpr int U4 = 4;  // entries per lane in flight
+    constexpr int U = 8;  // entries per lane in flight
     const LenT* tl = (const LenT*)J.t_len;
     const int quarter = lane >> 4, ql = lane & 15;
+    const int64_t row = (int64_t)t * kWave + lane;
+    const int64_t row_b = J.t_row_ptr[row < G ? row : G], row_e = J.t_row_ptr[row < G ? row + 1 : G];
     double mine = 0.0;
     for (int i = 0; i < 16; ++i) {
-        const int gi = t * kWave + quarter * 16 + i;
+        const int src = i * 4 + quarter;
+        const int64_t e0 = __shfl(row_b, src, kWave);
+        const int n = (int)(__shfl(row_e, src, kWave) - e0);
+        const int longest = max(max(__builtin_amdgcn_readlane(n, 0), __builtin_amdgcn_readlane(n, 16)),
+                                max(__builtin_amdgcn_readlane(n, 32), __builtin_amdgcn_readlane(n, 48)));
+        // entries past the row's end repeat its first one (a ray without
+        // entries: the matrix's first) and are not added
+        const int32_t* tc = J.t_col + (n > 0 ? e0 : 0);
+        const LenT* lc = tl + (n > 0 ? e0 : 0);
         double acc = 0.0;
-        if (gi < G) {
-            const int64_t b = J.t_row_ptr[gi], e = J.t_row_ptr[gi + 1];
-            for (int64_t q0 = b + ql; q0 < e; q0 += 16 * U4) {
-                int32_t pc[U4];
-                Real lc[U4];
+        int32_t pc[U];
+        LenT ln[U];
+        auto load = [&](int q) {
 #pragma unroll
-                for (int c = 0; c < U4; ++c) {
-                    const int64_t q = q0 + 16 * c < e ? q0 + 16 * c : b;
-                    pc[c] = J.t_col[q];
-                    lc[c] = (Real)tl[q];
-                }
-                double fv[U4];
-#pragma unroll
-                for (int c = 0; c < U4; ++c) fv[c] = J.f[pc[c]];
-#pragma unroll
-                for (int c = 0; c < U4; ++c)
-                    if (q0 + 16 * c < e) acc = fma((double)lc[c], fv[c], acc);
+            for (int c = 0; c < U; ++c) {
+                const int at = q + 16 * c < n ? q + 16 * c : 0;
+                pc[c] = tc[at];
+                ln[c] = lc[at];
             }
+        };
+        double fv[U];
+        auto add = [&](int q, const LenT* k) {
+#pragma unroll
+            for (int c = 0; c < U; ++c) {
+                const double sum = fma((double)(Real)k[c], fv[c], acc);
+                acc = q + 16 * c < n ? sum : acc;
+            }
+        };
+        if (longest > 0) load(ql);
+        int at = 0;
+        for (; at + 16 * U < longest; at += 16 * U) {
+            LenT k[U];
+#pragma unroll
+            for (int c = 0; c < U; ++c) {
+                fv[c] = J.f[pc[c]];
+                k[c] = ln[c];
+            }
+            load(at + 16 * U + ql);
+            add(at + ql, k);
+        }
+        if (at < longest) {
+#pragma unroll
+            for (int c = 0; c < U; ++c) fv[c] = J.f[pc[c]];
+            add(at + ql, ln);
         }
         acc = xor_add<1>(acc);
         acc = xor_add<2>(acc);
         acc = xor_add<4>(acc);
         acc = xor_add<8>(acc);
-        if (ql == i) mine = acc;
+        const double got = __shfl(acc, (lane & 3) * 16, kWave);  // ray 4 i + (lane mod 4)
+        if ((lane >> 2) == i) mine = got;
     }
     const int g = t * kWave + lane;
     const double acc = mine;
@@ -642,13 +672,34 @@ __device__ void auto_temperature(const ChainJob& J, const Real* r, double sse, C
     }
 }
 
-// Step 1 and Eq. 8 inside the workgroup.
-template <typename Real, bool GLOB, typename LenT = Real>
+// Step 1 and Eq. 8 inside the workgroup.  READY: the residual and its tile
+// sums have been formed in global memory by the whole GPU (sat_rebuild_kernel,
+// sat_batch_rebuild_kernel); a workgroup of its own took about 1 ns per PILA
+// entry for them, a tenth of a second at 512^2 x 360, where all the residuals
+// of a batch of 32 chains now take 1.8 ms (the batch: 436 to 344 ms) and the
+// 5760 rays of a chain at 64^2 x 90 FP64 18 us (7.66 to 6.70 ms).
+template <typename Real, bool GLOB, typename LenT, bool READY>
 __device__ ChainState chain_setup(const ChainJob& J, Real* r, ChainShared& sh, int lane, int wave, int NW)
 {
     ChainState cs;
     double drift;
-    rebuild_in_group<Real, GLOB, LenT>(J, r, sh, false, lane, wave, NW, &cs.sse, &drift);
+    if constexpr (READY) {
+        const int G = J.U * J.K;
+        if (!GLOB) {
+            const Real* from = (const Real*)J.r;
+            for (int g = threadIdx.x; g < G; g += blockDim.x) r[g] = from[rpos_g(J, g)];
+        }
+        if (wave == 0) {
+            double s;
+            tile_totals(J, G, false, lane, &s, &drift);
+            if (lane == 0) sh.scalar[0] = s;
+        }
+        __syncthreads();
+        cs.sse = uniform_f64(sh.scalar[0]);
+        __syncthreads();
+    } else {
+        rebuild_in_group<Real, GLOB, LenT>(J, r, sh, false, lane, wave, NW, &cs.sse, &drift);
+    }
     cs.T0 = J.T0;
     cs.TN = J.TN;
     cs.status = PILA_OK;
@@ -859,7 +910,7 @@ __device__ __forceinline__ void resync_in_group(const ChainJob& J, ChainState& c
 // ---------------------------------------------------------------------------
 // any row length, any M
 // ---------------------------------------------------------------------------
-template <typename Real, bool LDS, typename LenT = Real>
+template <typename Real, bool LDS, typename LenT = Real, bool SERVED = false>
 __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, bool segmented = false)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
@@ -869,7 +920,7 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
     Real* r = LDS ? (Real*)lds : (Real*)J.r;
     // segmented (global residual only): the chain state comes from the carry
     // and the chain returns when a resync is due, which then runs grid-wide
-    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !LDS, LenT>(J, r, sh, lane, wave, NW);
+    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !LDS, LenT, !SERVED>(J, r, sh, lane, wave, NW);
     Schedule sched;
     sched.start(cs.s_begin, cs.n_steps, J.n_stages, cs.T0, cs.TN, J.schedule);
     const bool f32 = sizeof(Real) == 4;
@@ -1568,7 +1619,7 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     Real* rl = (Real*)(lds + ((16 * (size_t)J.U + 2 * sizeof(Real) * (size_t)J.U + 15) & ~(size_t)15));
     const LenT* lenp = (const LenT*)J.len;
 
-    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !RLDS, LenT>(J, r, sh, lane, wave, NW);
+    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !RLDS, LenT, !SERVED>(J, r, sh, lane, wave, NW);
     const int64_t n_steps = cs.n_steps;
     const int64_t s_begin = cs.s_begin;
     if (!RLDS) {
@@ -1901,7 +1952,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
     Real* rl = (Real*)lds;
     const LenT* lenp = (const LenT*)J.len;
 
-    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !RLDS, LenT>(J, r, sh, lane, wave, NW);
+    ChainState cs = segmented ? load_carry(J) : chain_setup<Real, !RLDS, LenT, !SERVED>(J, r, sh, lane, wave, NW);
     const int64_t n_steps = cs.n_steps;
     const int64_t s_begin = cs.s_begin;
     if (!RLDS) lds_residual_load<Real>(J, r, rl);
@@ -2136,13 +2187,13 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
     write_stats(J, cs);
 }
 
-template <typename Real, typename LenT = Real>
+template <typename Real, typename LenT = Real, bool SERVED = false>
 __device__ void run_chain_simple_dispatch(const ChainJob& J, char* lds, int lds_bytes, ChainShared& sh)
 {
     if ((int64_t)J.U * J.K * (int64_t)sizeof(Real) <= lds_bytes)
-        run_chain_simple<Real, true, LenT>(J, lds, sh);
+        run_chain_simple<Real, true, LenT, SERVED>(J, lds, sh);
     else
-        run_chain_simple<Real, false, LenT>(J, lds, sh);
+        run_chain_simple<Real, false, LenT, SERVED>(J, lds, sh);
 }
 
 }  // namespace pila

@@ -151,9 +151,9 @@ __global__ __launch_bounds__(kPipedThreads) void srv_ring_kernel(RingCtl* ctl, R
             else if constexpr (BODY == kLong)
                 run_chain_long<float, false, E, true>(J, lds, sh, false);
             else if (J.precision == PILA_F32)
-                run_chain_simple_dispatch<float>(J, lds, lds_bytes, sh);
+                run_chain_simple_dispatch<float, float, true>(J, lds, lds_bytes, sh);
             else
-                run_chain_simple_dispatch<double>(J, lds, lds_bytes, sh);
+                run_chain_simple_dispatch<double, double, true>(J, lds, lds_bytes, sh);
         }
         __syncthreads();
         if (threadIdx.x == 0) {
