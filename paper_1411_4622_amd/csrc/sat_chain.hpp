@@ -51,6 +51,74 @@ struct ChainCarry {
     double sse, T0, TN, drift_r, drift_sse;
 };
 
+// Device memory, as the compiler has to know it.  A chain's descriptor is read
+// from memory by the batch and server kernels, and a plain pointer from there
+// may point anywhere: every access through it became a flat one, which counts
+// as an LDS access too, so each wait for LDS waited for the rows and residual
+// values asked for steps ahead (a batch of 32 FP32 chains: 325 ms with flat
+// accesses, 314 ms without).
+template <typename T>
+using Global = __attribute__((address_space(1))) T;
+
+template <typename T>
+struct GlobalPtr {
+    T* p;
+    __host__ __device__ operator T*() const { return p; }
+    __host__ __device__ T* operator->() const { return p; }
+    template <typename V>
+    __host__ __device__ explicit operator V*() const
+    {
+        return (V*)p;
+    }
+    template <typename I>
+    __device__ __forceinline__ auto& operator[](I i) const
+    {
+        return ((Global<T>*)p)[i];
+    }
+    __host__ __device__ GlobalPtr& operator=(T* q)
+    {
+        p = q;
+        return *this;
+    }
+};
+
+// p[i] of device memory (a class is one byte: LenQ)
+template <typename T, typename I>
+__device__ __forceinline__ T ldg(const T* p, I i)
+{
+    if constexpr (std::is_class<T>::value) {
+        static_assert(sizeof(T) == 1, "a byte");
+        const uint8_t raw = ((const Global<uint8_t>*)p)[i];
+        T v;
+        __builtin_memcpy(&v, &raw, 1);
+        return v;
+    } else {
+        return ((const Global<T>*)p)[i];
+    }
+}
+template <typename T, typename I>
+__device__ __forceinline__ void stg(T* p, I i, T v)
+{
+    ((Global<T>*)p)[i] = v;
+}
+// a value of a residual that is in global memory (GLOB) or in LDS
+template <bool GLOB, typename T, typename I>
+__device__ __forceinline__ T ldr(const T* r, I i)
+{
+    if constexpr (GLOB)
+        return ldg(r, i);
+    else
+        return r[i];
+}
+template <bool GLOB, typename T, typename I>
+__device__ __forceinline__ void str(T* r, I i, T v)
+{
+    if constexpr (GLOB)
+        stg(r, i, v);
+    else
+        r[i] = v;
+}
+
 struct ChainJob {
     int32_t N, U, K, P;
     int32_t precision, m_cand, n_stages, q_auto;
@@ -63,25 +131,25 @@ struct ChainJob {
     int64_t n_steps, resync_every;
     uint64_t seed, chain_id;
     double T0, TN, tn_ratio, delta_max, f_min, f_max, ln09;
-    const int64_t* row_ptr;
-    const int32_t* col;
-    const void* len;
-    const int64_t* t_row_ptr;
-    const int32_t* t_col;
-    const void* t_len;
-    const int32_t* support;
-    const double* sino;
-    double* f;
-    void* r;          // residual, U*K values of the chain's precision (global mode)
-    double* tsum;     // per 64-ray tile: sum of squared residuals (ceil(U*K/64))
-    double* tdrift;   // per tile: max |r_old - r64| at a rebuild
-    ChainCarry* carry;
-    sat_stats* stats;
-    int32_t* tr_m;
-    uint8_t* tr_acc;
-    double* tr_dc;
-    const int32_t* tcol;     // optional: per PILA entry, the slot word of ray_slot (else NULL)
-    const uint64_t* cancel;  // served chains: host word that equals cancel_tag once cancelled
+    GlobalPtr<const int64_t> row_ptr;
+    GlobalPtr<const int32_t> col;
+    GlobalPtr<const void> len;
+    GlobalPtr<const int64_t> t_row_ptr;
+    GlobalPtr<const int32_t> t_col;
+    GlobalPtr<const void> t_len;
+    GlobalPtr<const int32_t> support;
+    GlobalPtr<const double> sino;
+    GlobalPtr<double> f;
+    GlobalPtr<void> r;          // residual, U*K values of the chain's precision (global mode)
+    GlobalPtr<double> tsum;     // per 64-ray tile: sum of squared residuals (ceil(U*K/64))
+    GlobalPtr<double> tdrift;   // per tile: max |r_old - r64| at a rebuild
+    GlobalPtr<ChainCarry> carry;
+    GlobalPtr<sat_stats> stats;
+    GlobalPtr<int32_t> tr_m;
+    GlobalPtr<uint8_t> tr_acc;
+    GlobalPtr<double> tr_dc;
+    GlobalPtr<const int32_t> tcol;     // optional: per PILA entry, the slot word of ray_slot (else NULL)
+    GlobalPtr<const uint64_t> cancel;  // served chains: host word that equals cancel_tag once cancelled
     uint64_t cancel_tag;
 };
 
@@ -154,7 +222,7 @@ constexpr int64_t kCancelEvery = 1024;
 __device__ __forceinline__ void cancel_probe(const ChainJob& J, ChainShared& sh, int64_t s)
 {
     if (J.cancel && (s & (kCancelEvery - 1)) == 0 && threadIdx.x == 0)
-        sh.stop = __hip_atomic_load(J.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == J.cancel_tag;
+        sh.stop = __hip_atomic_load(J.cancel.p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == J.cancel_tag;
 }
 __device__ __forceinline__ bool cancel_seen(const ChainJob& J, const ChainShared& sh, int64_t s)
 {
@@ -234,17 +302,22 @@ __device__ __forceinline__ T xor_add(T x)
     }
 }
 
-template <int O>
-__device__ __forceinline__ double xor_min(double x)
+template <int O, typename T>
+__device__ __forceinline__ T xor_min(T x)
 {
-    double a, b;
+    T a, b;
     if constexpr (O == 16 || O == 32) {
         swap_pair<O>(x, &a, &b);
     } else {
         a = x;
         b = xor_partner<O>(x);
     }
-    return b < a ? b : a;
+    // (no NaN comes here; the library's minimum first quiets its arguments)
+    if constexpr (sizeof(T) == 4)
+        asm("v_min_f32 %0, %1, %2" : "=v"(a) : "v"(a), "v"(b));
+    else
+        asm("v_min_f64 %0, %1, %2" : "=v"(a) : "v"(a), "v"(b));
+    return a;
 }
 
 template <int O, int LPC, int K, typename T>
@@ -304,6 +377,11 @@ __device__ __forceinline__ double readlane_f64(double v, int l)
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
     return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double readlane_real(double v, int l) { return readlane_f64(v, l); }
+__device__ __forceinline__ float readlane_real(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 // A uniform value kept in a vector register (the step loops run out of scalar
 // ones first, and a spilled scalar costs two vector operations)
@@ -408,7 +486,7 @@ struct Schedule {
     }
     __device__ double at(int64_t s)
     {
-        if (s >= next) {
+        if (__builtin_expect(s >= next, 0)) {
             while (s >= next) {
                 ++stage;
                 whole += quot;
@@ -468,11 +546,11 @@ __device__ Real estimate_sum(const ChainJob& J, const Real* __restrict__ r, uint
         for (int c = 0; c < U; ++c) {
             const int64_t q = q0 + (int64_t)c * kWave < e ? q0 + (int64_t)c * kWave : b;
             cc[c] = J.col[q];
-            ll[c] = (Real)len[q];
+            ll[c] = (Real)ldg(len, q);
         }
         Real rr[U];
 #pragma unroll
-        for (int c = 0; c < U; ++c) rr[c] = r[ridx<GLOB>(J, cc[c])];
+        for (int c = 0; c < U; ++c) rr[c] = ldr<GLOB>(r, ridx<GLOB>(J, cc[c]));
 #pragma unroll
         for (int c = 0; c < U; ++c) {
             if (q0 + (int64_t)c * kWave < e) {
@@ -517,7 +595,7 @@ __device__ void rebuild_tile(const ChainJob& J, Real* __restrict__ r, int G, int
                                 max(__builtin_amdgcn_readlane(n, 32), __builtin_amdgcn_readlane(n, 48)));
         // entries past the row's end repeat its first one (a ray without
         // entries: the matrix's first) and are not added
-        const int32_t* tc = J.t_col + (n > 0 ? e0 : 0);
+        const int32_t* tc = J.t_col.p + (n > 0 ? e0 : 0);
         const LenT* lc = tl + (n > 0 ? e0 : 0);
         double acc = 0.0;
         int32_t pc[U];
@@ -526,8 +604,8 @@ __device__ void rebuild_tile(const ChainJob& J, Real* __restrict__ r, int G, int
 #pragma unroll
             for (int c = 0; c < U; ++c) {
                 const int at = q + 16 * c < n ? q + 16 * c : 0;
-                pc[c] = tc[at];
-                ln[c] = lc[at];
+                pc[c] = ldg(tc, at);
+                ln[c] = ldg(lc, at);
             }
         };
         double fv[U];
@@ -568,8 +646,8 @@ __device__ void rebuild_tile(const ChainJob& J, Real* __restrict__ r, int G, int
     if (g < G) {
         const double r64 = acc - J.sino[g];
         const uint32_t at = ridx<GLOB>(J, g);
-        if (measure) dr = fabs((double)r[at] - r64);
-        r[at] = (Real)r64;
+        if (measure) dr = fabs((double)ldr<GLOB>(r, at) - r64);
+        str<GLOB>(r, at, (Real)r64);
         sq = r64 * r64;
     }
     sq = wave_canon_sum(sq);
@@ -687,7 +765,7 @@ __device__ ChainState chain_setup(const ChainJob& J, Real* r, ChainShared& sh, i
         const int G = J.U * J.K;
         if (!GLOB) {
             const Real* from = (const Real*)J.r;
-            for (int g = threadIdx.x; g < G; g += blockDim.x) r[g] = from[rpos_g(J, g)];
+            for (int g = threadIdx.x; g < G; g += blockDim.x) r[g] = ldg(from, rpos_g(J, g));
         }
         if (wave == 0) {
             double s;
@@ -812,38 +890,36 @@ __device__ __forceinline__ bool accepts(double dC, double T, double invT, double
 // over the checked range) and settled by it when -dC / T and ln N1 differ by
 // more than 4e-6 relative; the FP64 square roots and divisions of Eq. 7 run
 // only inside that band.  (With both square roots and three divisions formed
-// for every lane the decision took 1200 clocks of a step, now 640: 64 x 64,
+// for every lane the decision took 1200 clocks of a step, then 640: 64 x 64,
 // 90 angles, M = 4, FP64.)
+template <typename Real>
 __device__ __forceinline__ Decision decide(double S, int M, int lane, double sse, double KU, double invKU,
                                            double T, double invT, double N1, double lnN1)
 {
-    const double v = lane < M && S == S ? S : INFINITY;
-    double vmin = xor_min<8>(xor_min<4>(xor_min<2>(xor_min<1>(v))));
+    // (an FP32 chain's sums are FP32 values: their minimum takes half the work)
+    const Real v = lane < M && S == S ? (Real)S : (Real)INFINITY;
+    Real vmin = xor_min<8>(xor_min<4>(xor_min<2>(xor_min<1>(v))));
     if (M > 16)
         vmin = xor_min<32>(xor_min<16>(vmin));
     else
-        vmin = readlane_f64(vmin, 0);  // every estimate is in the first 16 lanes
+        vmin = readlane_real(vmin, 0);  // every estimate is in the first 16 lanes
     const unsigned long long mask = __ballot(v == vmin);
     Decision dn;
     dn.ms = uniform_i32(__ffsll((long long)mask) - 1);
-    dn.S = readlane_f64(v, dn.ms);
+    dn.S = (double)readlane_real(v, dn.ms);
     const bool finite = sse >= 0.0 && sse < INFINITY;
     if (finite && dn.S <= 0.0) {
         dn.accept = true;
         return dn;
     }
-    if (finite) {
+    if (__builtin_expect(finite, 1)) {
         const float n = (float)(dn.S * invKU), b = (float)(sse * invKU), a = (float)((sse + dn.S) * invKU);
-        if (n > 1e-30f && a < 1e30f) {
+        if (__builtin_expect(n > 1e-30f && a < 1e30f, 1)) {
             const float den = __builtin_amdgcn_sqrtf(a) + __builtin_amdgcn_sqrtf(b);
             const float x = -n * __builtin_amdgcn_rcpf(den) * (float)invT, y = (float)lnN1;
             const float margin = 4e-6f * (fabsf(x) + fabsf(y));
-            if (x < y - margin) {
-                dn.accept = false;
-                return dn;
-            }
-            if (x > y + margin) {
-                dn.accept = true;
+            if (__builtin_expect(fabsf(x - y) > margin, 1)) {
+                dn.accept = x > y;
                 return dn;
             }
         }
@@ -876,7 +952,7 @@ struct Trace {
         S = here ? dn.S : S;
         sse = here ? sse_before : sse;
         m = here ? (dn.accept ? dn.ms : -1 - dn.ms) : m;
-        if ((s & (kWave - 1)) == kWave - 1) store(J, s + 1, lane, KU);
+        if (__builtin_expect((s & (kWave - 1)) == kWave - 1, 0)) store(J, s + 1, lane, KU);
     }
 };
 
@@ -1030,15 +1106,15 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
                     const int64_t qa = bb[0] + (o + c * kWave < la ? o + c * kWave : 0);
                     const int64_t qb = bb[1] + (o + c * kWave < lb ? o + c * kWave : 0);
                     ca[c] = J.col[qa];
-                    la_[c] = (Real)lenp[qa];
+                    la_[c] = (Real)ldg(lenp, qa);
                     cb[c] = J.col[qb];
-                    lb_[c] = (Real)lenp[qb];
+                    lb_[c] = (Real)ldg(lenp, qb);
                 }
                 Real ra[U], rb[U];
 #pragma unroll
                 for (int c = 0; c < U; ++c) {
-                    ra[c] = r[ridx<!LDS>(J, ca[c])];
-                    rb[c] = r[ridx<!LDS>(J, cb[c])];
+                    ra[c] = ldr<!LDS>(r, ridx<!LDS>(J, ca[c]));
+                    rb[c] = ldr<!LDS>(r, ridx<!LDS>(J, cb[c]));
                 }
 #pragma unroll
                 for (int c = 0; c < U; ++c) {
@@ -1085,7 +1161,7 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
         cancel_probe(J, sh, s);
         __syncthreads();
         const double dv = sh.d[lane];  // with the sums, so that no second LDS trip follows the decision
-        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
+        const Decision dn = decide<Real>(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
         const double d_star = readlane_f64(dv, dn.ms);
         // Eq. 6 for the winner, by the whole workgroup (one entry per thread;
         // the row's rays are distinct, so no two threads touch one value); an
@@ -1095,7 +1171,7 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
             const Real dr = (Real)d_star;
             for (int64_t q = b + threadIdx.x; q < e; q += blockDim.x) {
                 const uint32_t at = ridx<!LDS>(J, J.col[q]);
-                r[at] = r[at] + dr * (Real)lenp[q];
+                str<!LDS>(r, at, ldr<!LDS>(r, at) + dr * (Real)ldg(lenp, q));
             }
             if (threadIdx.x == 0) J.f[sh.p[dn.ms]] = sh.fn[dn.ms];
         }
@@ -1388,7 +1464,7 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
         }
         const double dv = sp.d[pb][lane], fv = sp.fn[pb][lane];
         const int32_t pv = sp.p[pb][lane];
-        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
+        const Decision dn = decide<Real>(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, N1, lnN1);
         const double d_star = readlane_f64(dv, dn.ms);
         const bool change = dn.accept && d_star != 0.0;
         int32_t pstar = 0;
@@ -1456,12 +1532,12 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
 template <typename T>
 __device__ __forceinline__ T ld32(const T* base, uint32_t i)
 {
-    return *(const T*)((const char*)base + i * (uint32_t)sizeof(T));
+    return ldg((const T*)((const char*)base + i * (uint32_t)sizeof(T)), 0);
 }
 template <typename T>
 __device__ __forceinline__ void st32(T* base, uint32_t i, T v)
 {
-    *(T*)((char*)base + i * (uint32_t)sizeof(T)) = v;
+    stg((T*)((char*)base + i * (uint32_t)sizeof(T)), 0, v);
 }
 
 // A length loaded a step or two before it is used: FP32 lengths as they are;
@@ -1522,25 +1598,12 @@ __device__ __forceinline__ void wait_loads()
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 }
 
-// What drawing a block of estimates needs of the chain's descriptor.  Read
-// where it is used from the descriptor in constant memory, when the caller
-// has it there (the address made opaque, so that the fields are not held in
-// scalar registers, which the step loop has too few of).
-struct DrawArgs {
-    uint64_t seed, chain_id;
-    const int32_t* support;
-    const int64_t* row_ptr;
-    double delta_max;
-    int32_t P;
-};
-typedef const __attribute__((address_space(4))) ChainJob* ConstJob;
-
 template <typename Real, int E>
 struct RowSet {
     int32_t col[E];
     Real len[E];
     int32_t tk[E];  // where each ray's residual lives: LDS index (flagged) or patch slot
-    Real rv[E];     // residual values of the row's rays
+    Real rv[E];     // residual values of the row's rays (in global memory)
     double fo;      // image value of the pixel
     int32_t p, n;   // pixel, row length
     double delta;   // proposed change before the clamp
@@ -1565,7 +1628,7 @@ __device__ void lds_residual_load(const ChainJob& J, const Real* r, Real* rl)
     const int n = J.UL * J.Kc;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int u = i / J.Kc, k = J.k_lo + i % J.Kc;
-        rl[i] = r[rpos(J, u, k)];
+        rl[i] = ldg(r, rpos(J, u, k));
     }
 }
 template <typename Real>
@@ -1574,7 +1637,7 @@ __device__ void lds_residual_store(const ChainJob& J, Real* r, const Real* rl)
     const int n = J.UL * J.Kc;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int u = i / J.Kc, k = J.k_lo + i % J.Kc;
-        r[rpos(J, u, k)] = rl[i];
+        stg(r, rpos(J, u, k), rl[i]);
     }
 }
 
@@ -1587,21 +1650,19 @@ __device__ void lds_residual_store(const ChainJob& J, Real* r, const Real* rl)
 // Either way the same float results.
 template <typename Real, bool RLDS, int CPW, int E, bool SERVED = false, bool TK = false, typename LenT = Real,
           bool LATE = false>
-__device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, bool segmented,
-                                ConstJob constant = nullptr)
+__device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, bool segmented)
 {
-    auto draw_args = [&]() -> DrawArgs {
-        if (constant) {
-            ConstJob p = constant;
-            asm volatile("" : "+s"(p));
-            return {p->seed, p->chain_id, p->support, p->row_ptr, p->delta_max, p->P};
-        }
-        return {J.seed, J.chain_id, J.support, J.row_ptr, J.delta_max, J.P};
-    };
     constexpr int LPC = kWave / CPW;  // lanes per estimate
     constexpr int BL = kWave / CPW;   // steps per block of draws
     constexpr int kLdsFlag = kRaySlotLds;
     constexpr bool kTK = TK && !RLDS;
+    // Several estimates a wavefront: a set's next row is asked for at the end
+    // of its step, while the winner's owner writes, a step and a half before
+    // it is used (256 x 256, 180 angles, M = 16, FP32: 51.1 to 48.7 ms).  One
+    // estimate a wavefront: the owner's longer writes and the row loads then
+    // add up (a batch of 32 chains: 318 to 330 ms), so it is asked for before
+    // the step's first barrier.
+    constexpr bool kRowsLate = CPW > 1 && !RLDS;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
     const int slot = lane / LPC, li = lane % LPC;
     const double KU = (double)J.K * (double)J.U;
@@ -1629,12 +1690,14 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     Schedule sched;
     sched.start(s_begin, n_steps, J.n_stages, cs.T0, cs.TN, J.schedule);
 
+    // (What a step seldom does is marked unlikely, here and in decide and the
+    // schedule, so that its code lies out of the step's way: some 2000 of a
+    // step's 2700 instructions.)
     // The draws of a block of steps, in two stages so that neither waits for
     // memory: the estimates (and the support lookup issued), later the row
     // offsets.  Steps past the end draw nothing and have empty rows.
     Draws cur, nxt;
     auto draw = [&](Draws& D, int32_t block) {
-        const DrawArgs C = draw_args();
         const int64_t s = (int64_t)block * BL + lane / CPW;
         const int m = wave * CPW + lane % CPW;
         D.drawn = block;
@@ -1644,13 +1707,15 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         D.lnN1 = 0.0;
         // the key is made opaque here, so that the round keys are formed per
         // block instead of being held in scalar registers across the loop
-        uint64_t k0 = lane0(C.seed), k1 = lane0(C.chain_id);
-        asm volatile("" : "+s"(k0), "+s"(k1));
+        uint64_t k0 = J.seed, k1 = J.chain_id;
+        asm volatile("" : "+v"(k0), "+v"(k1));
+        k0 = lane0(k0);
+        k1 = lane0(k1);
         if (s < n_steps) {
             if (m < M) {
                 const Words4 w = philox4x64(k0, k1, (uint64_t)s, (uint64_t)m, 0, 0);
-                D.p = C.support[__umul64hi(w.w0, (uint64_t)C.P)];
-                D.delta = C.delta_max * (2.0 * unit53(w.w1) - 1.0);
+                D.p = J.support[__umul64hi(w.w0, (uint64_t)J.P)];
+                D.delta = J.delta_max * (2.0 * unit53(w.w1) - 1.0);
             }
             if (lane % CPW == 0) {
                 D.N1 = unit53(philox4x64(k0, k1, (uint64_t)s, 0, 1, 0).w0);
@@ -1659,12 +1724,11 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         }
     };
     auto offsets = [&](Draws& D, int32_t block) {
-        const DrawArgs C = draw_args();
         D.block = block;
         const bool on = (int64_t)block * BL + lane / CPW < n_steps && wave * CPW + lane % CPW < M;
-        const int64_t b0 = C.row_ptr[D.p];
+        const int64_t b0 = J.row_ptr[D.p];
         D.b = (uint32_t)b0;
-        D.n = on ? (int32_t)(C.row_ptr[D.p + 1] - b0) : 0;
+        D.n = on ? (int32_t)(J.row_ptr[D.p + 1] - b0) : 0;
     };
 
     // the draws to go on from step t
@@ -1682,10 +1746,10 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     // them, and each step waited for the rows it had just asked for.
     auto prefetch = [&](RowSet<Real, E>& S, int64_t t) {
         const int32_t block = uniform_i32((int32_t)(t / BL));
-        if (cur.block != block) cur = nxt;
+        if (__builtin_expect(cur.block != block, 0)) cur = nxt;
         const int j = uniform_i32((int)t & (BL - 1));
-        if (j >= BL / 4 && nxt.drawn != block + 1) draw(nxt, block + 1);  // the next block's, early
-        if (j >= BL / 2 && nxt.block != block + 1) offsets(nxt, block + 1);
+        if (__builtin_expect(j >= BL / 4 && nxt.drawn != block + 1, 0)) draw(nxt, block + 1);  // the next block's, early
+        if (__builtin_expect(j >= BL / 2 && nxt.block != block + 1, 0)) offsets(nxt, block + 1);
         uint32_t b;
         if constexpr (CPW == 1) {  // one estimate a wavefront: the draw's lane is the step's
             S.p = in_vector(__builtin_amdgcn_readlane(cur.p, j));
@@ -1706,9 +1770,9 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
             const int q = li + e * LPC;
             const uint32_t at = q < S.n ? b + (uint32_t)q : 0u;
             if (kTK)
-                S.tk[e] = ld32(J.tcol, at);
+                S.tk[e] = ld32(J.tcol.p, at);
             else
-                S.col[e] = ld32(J.col, at);
+                S.col[e] = ld32(J.col.p, at);
             S.len[e] = LATE ? len_hold<Real, LenT>(lenp, at) : (Real)ld32(lenp, at);
         }
     };
@@ -1731,6 +1795,16 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     auto lenv = [&](Real v) -> Real {
         if constexpr (LATE) return len_use<Real, LenT>(v);
         return v;
+    };
+
+    // the value of a ray in the LDS part (for any other, some word of LDS)
+    auto lget = [&](int tk) -> Real { return in_lds(tk) ? rl[tk & ~kLdsFlag] : pval[0]; };
+    // the values of a set that is scored next, before the loop or after a resync
+    auto first_value = [&](RowSet<Real, E>& S, int e) {
+        if (in_lds(S.tk[e]))
+            S.rv[e] = rl[S.tk[e] & ~kLdsFlag];
+        else
+            S.rv[e] = rget(gcol(S, e));
     };
 
     RowSet<Real, E> A, B, C;
@@ -1798,14 +1872,14 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
             sh.p[m_mine] = X.p;
         }
         // the rows of step s + 2
-        prefetch(Z, s + 2);
+        if (!kRowsLate) prefetch(Z, s + 2);
         if (SERVED) cancel_probe(J, sh, s);
         __syncthreads();
         // every estimate's pixel and values with the sums, so that no second
         // LDS trip follows the decision
         const double dv = sh.d[lane], fv = sh.fn[lane];
         const int32_t pv = sh.p[lane];
-        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
+        const Decision dn = decide<Real>(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
         const double d_star = readlane_f64(dv, dn.ms);
         // an accepted zero change leaves image and residual as they are
         const bool changed = dn.accept && d_star != 0.0;
@@ -1816,13 +1890,15 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
                     const Real rn = X.rv[e] + dr * lenv(X.len[e]);
                     if (RLDS) {
                         r[X.col[e]] = rn;
-                    } else if (X.tk[e] & kLdsFlag) {
-                        rl[X.tk[e] & ~kLdsFlag] = rn;
                     } else {
-                        st32(r, gcol(X, e), rn);
-                        const int ps = slot_patch(X.tk[e]);
-                        pkey[ps] = ((int64_t)s << kSlotPosBits) | (X.tk[e] & kSlotPosMask);
-                        pval[ps] = rn;
+                        // into the residual's LDS part or the patch table
+                        const int tk = X.tk[e], ps = slot_patch(tk);
+                        Real* at = tk & kLdsFlag ? rl + (tk & ~kLdsFlag) : pval + ps;
+                        *at = rn;
+                        if (!(tk & kLdsFlag)) {
+                            pkey[ps] = ((int64_t)s << kSlotPosBits) | (tk & kSlotPosMask);
+                            st32(r, gcol(X, e), rn);
+                        }
                     }
                 }
             }
@@ -1830,7 +1906,7 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         }
         if (traced) trace.add(J, dn, cs.sse, s, lane, KU);
         count_decision(cs, dn, d_star);
-        if (sizeof(Real) == 4 && J.resync_every > 0 && cs.since >= J.resync_every) {
+        if (sizeof(Real) == 4 && __builtin_expect(J.resync_every > 0 && cs.since >= J.resync_every, 0)) {
             if (!RLDS) {
                 __syncthreads();
                 lds_residual_store<Real>(J, r, rl);
@@ -1847,15 +1923,17 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
             draws_from(s + 1);
             prefetch(Y, s + 1);
             prefetch(Z, s + 2);
+            if (kRowsLate) prefetch(X, s + 3);
             table_slots(Y);
             __syncthreads();
 #pragma unroll
-            for (int e = 0; e < E; ++e) Y.rv[e] = in_lds(Y.tk[e]) ? rl[Y.tk[e] & ~kLdsFlag] : rget(gcol(Y, e));
+            for (int e = 0; e < E; ++e) first_value(Y, e);
             Y.fo = J.f[Y.p];
             lp = -1;
             patch = false;
             return false;
         }
+        if (kRowsLate) prefetch(X, s + 3);  // (this set has been used)
         __syncthreads();
         if (changed) {
             lp = __builtin_amdgcn_readlane(pv, dn.ms);
@@ -1886,9 +1964,10 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         prefetch(A, s_begin);
         table_slots(A);
 #pragma unroll
-        for (int e = 0; e < E; ++e) A.rv[e] = in_lds(A.tk[e]) ? rl[A.tk[e] & ~kLdsFlag] : rget(gcol(A, e));
+        for (int e = 0; e < E; ++e) first_value(A, e);
         A.fo = J.f[A.p];
         prefetch(B, s_begin + 1);
+        if (kRowsLate) prefetch(C, s_begin + 2);
         wait_loads();
         for (int64_t s = s_begin;;) {
             if (step(A, B, C, s)) {
@@ -2010,7 +2089,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
         for (int e = 0; e < E; ++e) {
             const int q = lane + e * kWave;
             const uint32_t at = q < S.n ? b + (uint32_t)q : 0u;
-            S.col[e] = ld32(J.col, at);
+            S.col[e] = ld32(J.col.p, at);
             S.len[e] = LATE ? len_hold<Real, LenT>(lenp, at) : (Real)ld32(lenp, at);
         }
     };
@@ -2092,7 +2171,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
         for (int q = kWave * E + lane; q < X.n; q += kWave) {
             int lo;
             const Real t = dr * (Real)ld32(lenp, X.b + (uint32_t)q);
-            part[0] = fma(t, (Real)2 * rget(ld32(J.col, X.b + (uint32_t)q), &lo) + t, part[0]);
+            part[0] = fma(t, (Real)2 * rget(ld32(J.col.p, X.b + (uint32_t)q), &lo) + t, part[0]);
         }
         const Real S = canon_sum<kWave>(part);
         if (active && lane == 0) {
@@ -2102,7 +2181,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
         if (SERVED) cancel_probe(J, sh, s);
         __syncthreads();
         const double dv = sh.d[lane];  // with the sums, so that no second LDS trip follows the decision
-        const Decision dn = decide(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
+        const Decision dn = decide<Real>(sh.S[lane], M, lane, cs.sse, KU, invKU, T, invT, X.N1, X.lnN1);
         const double d_star = readlane_f64(dv, dn.ms);
         const bool changed = dn.accept && d_star != 0.0;
         if (changed && dn.ms == wave) {  // the owner of the winner applies Eq. 6
@@ -2121,7 +2200,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
             // the entries beyond the registers: their rays differ from the
             // row's others, so their values are still the ones summed
             for (int q = kWave * E + lane; q < X.n; q += kWave) {
-                const int32_t g = ld32(J.col, X.b + (uint32_t)q);
+                const int32_t g = ld32(J.col.p, X.b + (uint32_t)q);
                 int lo;
                 const Real rn = rget(g, &lo) + dr * (Real)ld32(lenp, X.b + (uint32_t)q);
                 if (RLDS)
