@@ -99,7 +99,14 @@ __device__ __forceinline__ T ldg(const T* p, I i)
 template <typename T, typename I>
 __device__ __forceinline__ void stg(T* p, I i, T v)
 {
-    ((Global<T>*)p)[i] = v;
+    if constexpr (std::is_class<T>::value) {
+        static_assert(sizeof(T) == 1, "a byte");
+        uint8_t raw;
+        __builtin_memcpy(&raw, &v, 1);
+        ((Global<uint8_t>*)p)[i] = raw;
+    } else {
+        ((Global<T>*)p)[i] = v;
+    }
 }
 // a value of a residual that is in global memory (GLOB) or in LDS
 template <bool GLOB, typename T, typename I>
