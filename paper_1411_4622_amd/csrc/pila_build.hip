@@ -27,7 +27,7 @@
 // 2.45, ray fill 2.4 ms.  Counting and filling by evaluating the full chord at
 // four candidate bins per (pixel, angle), the rays by a lane per image row,
 // and one-workgroup scans took 31.9 ms (4.1 + 6.2, 6.1, 11.5, 1.9 ms);
-// 512 x 512 x 360: 4.91 -> 1.00 ms, 64 x 64 x 60: 228 -> 116 us.  The fills
+// 512 x 512 x 360: 4.91 -> 0.97 ms, 64 x 64 x 60: 228 -> 106 us.  The fills
 // without their stores take 1.5 ms each (FP64 arithmetic, 1.1 ms of issue).
 // Collecting a row's entries in LDS and storing whole cache lines was
 // measured (2.2 and 2.6 ms; slower at 512 x 512) and not kept.
@@ -44,7 +44,12 @@ namespace pila {
 namespace {
 
 constexpr int kWavesPerBlock = 4;
-constexpr int kScanChunk = 256;       // rows per count block and scan chunk
+// Rows per count block and scan chunk: one wavefront's, so that the 16
+// wavefronts of a count block share a row's angles or steps 16 ways and small
+// geometries have a block for more compute units.  Whole builds with 256 and
+// with 64: 64 x 64, 60 angles 125 and 114 us; 128 x 128, 90 angles 153 and 140;
+// 256 x 256, 180 angles 306 and 258; 512 x 512, 360 angles 1.01 and 0.97 ms.
+constexpr int kScanChunk = 64;
 constexpr double kEdgeBand = 1e-8;    // centre distances this close to the edge: evaluate the length
 
 // The support as the kernels read it, uploaded by each phase: per image row a
@@ -223,9 +228,9 @@ __device__ __forceinline__ RayLine ray_line(int N, double c, double s, double sk
 }
 
 // ---------------------------------------------------------------------------
-// phase 1: counts, scanned within each block's 256 rows
+// phase 1: counts, scanned within each block's 64 rows
 // ---------------------------------------------------------------------------
-constexpr int kCountThreads = 1024;  // 16 wavefronts per 256 rows, so that small geometries have enough of them
+constexpr int kCountThreads = 1024;
 constexpr int kParts = kCountThreads / kScanChunk;
 
 // entries of pixel (i, j) at the angles u0 .. u1 - 1: lane = pixel, all lanes
@@ -319,9 +324,9 @@ __device__ int count_ray(bool on, int N, double c, double s, double sk, const Ma
     return n;
 }
 
-// Blocks [0, pixel_blocks): 256 pixels each, a quarter of the angles per 256
-// threads; the rest: 256 rays each, a quarter of the steps per 256 threads.  A block leaves its
-// rows' counts scanned within the block (inclusive), so the last row of each
+// Blocks [0, pixel_blocks): 64 pixels each, a sixteenth of the angles per
+// wavefront; the rest: 64 rays each, a sixteenth of the steps per wavefront.  A
+// block leaves its rows' counts scanned within the block (inclusive), so the last row of each
 // chunk holds the chunk's total.  max_row: longest pixel row.
 __global__ __launch_bounds__(kCountThreads, 8) void count_kernel(int32_t N, int32_t U, int32_t K,
                                                               const double* __restrict__ trig, MaskView mv,

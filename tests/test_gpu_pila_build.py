@@ -58,6 +58,8 @@ ANGLES = {
     (130, 16, 20, "steep", "gaps", "f64"),      # a detector narrower than the image
     (130, 3, 400, "uniform", "circle", "f64"),  # and wider
     (257, 37, 364, "uniform", "gaps", "f32"),   # a row beyond a scan chunk
+    (8, 16, 4, "steep", "full", "f64"),         # one chunk of pixels and one of rays, both full
+    (9, 5, 13, "uniform", "gaps", "f32"),       # a ray beyond a chunk
 ])
 def test_build_matches_the_oracle(P, N, U, K, angles, mask, dtype):
     print("build N=%d U=%d K=%d %s %s %s" % (N, U, K, angles, mask, dtype), flush=True)
