@@ -34,6 +34,7 @@ namespace {
 struct SeqArgs {
     int32_t U, K, P, n_iter;
     int64_t m_per;
+    int64_t n_pixels;
     double lambda;
     uint64_t seed;
     const int64_t* row_ptr;
@@ -232,7 +233,11 @@ __global__ __launch_bounds__(64) void sirt_seq_kernel(SeqArgs A)
             ++it;
         }
     };
-    if (total == 0) {  // iterations without updates: the cost of the start
+    // Every iteration has the cost of the start: there are no updates, or the
+    // PILA has no entries (no ray meets the support), so that none would
+    // change anything; the steps' loads, which read entry 0 in the place of
+    // those that a row does not have, would find no entry there.
+    if (total == 0 || A.row_ptr[A.n_pixels] == 0) {
         if (A.cost) {
             double sq = 0.0;
             for (int64_t g = lane; g < G; g += kWave) {
@@ -295,6 +300,7 @@ int32_t seq_impl(const pila_geom* geom, const pila_csr* csr, const double* d_sin
     A.P = csr->n_support;
     A.n_iter = prm->n_iter;
     A.m_per = prm->m_per;
+    A.n_pixels = (int64_t)geom->n * geom->n;
     A.lambda = prm->lambda;
     A.seed = prm->seed;
     A.row_ptr = csr->row_ptr;
