@@ -1098,6 +1098,10 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
                         bb[h] = J.row_ptr[pp[h]];
                         ee[h] = J.row_ptr[pp[h] + 1];
                     }
+                    // the loads below read a row's first entry in the place of
+                    // those past its end; a row without entries may begin at
+                    // the arrays' end, so it is taken to begin at entry 0
+                    if (ee[h] == bb[h]) bb[h] = ee[h] = 0;
                     dd[h] = propose(s, m, pp[h], delta, &fnn[h]);
                 }
             }
