@@ -141,11 +141,12 @@ int device_props(hipDeviceProp_t* prop)
 bool piped_allowed(const pila_geom* g, const pila_csr* c)
 {
     // ray index g = u K + k below 2^24 (the multiply-shift split), bins
-    // below 8192 (the patch-table tag), and 32-bit byte offsets into the rows
+    // below 8192 (the patch-table tag), and 32-bit byte offsets into the rows:
+    // into the lengths and into the four-byte ray indices and slot words
     const int64_t G = (int64_t)g->n_angles * g->n_bins;
-    const int64_t lb = len_bytes(g->len_dtype);
+    const int64_t widest = std::max(len_bytes(g->len_dtype), (int)sizeof(int32_t));
     return c->nnz >= 1 && c->max_row >= 1 && g->n_bins < 8192 && G < (1 << 24) &&
-           c->nnz * lb <= ((int64_t)1 << 32);
+           c->nnz <= ((int64_t)1 << 32) / widest;
 }
 
 // LDS of a pipelined chain whose residual is not wholly in LDS: the patch
