@@ -59,16 +59,18 @@ __device__ __forceinline__ XcdRows xcd_rows(int64_t n, int w)
 // would be 1.3 ms): forward 4.05 -> 2.11 ms, back 4.85 -> 2.66 ms; 256 x 256 x
 // 180: 45 -> 31 and 56 -> 31 us.  (Eight rows at once but 64 lanes on each:
 // 2.41 and 2.94 ms.)
-template <typename LenT, int V>
-__global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+template <typename LenT>
+__global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, const int64_t* __restrict__ rp,
                                                          const int32_t* __restrict__ ci,
                                                          const LenT* __restrict__ ln,
                                                          const double* __restrict__ x, double* __restrict__ out)
 {
-    constexpr int R = 8, L = 64 / R;
+    constexpr int R = 8, L = 64 / R, V = 4;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const XcdRows xr = xcd_rows<R>(n, w);
+    const int64_t last = rp[n] - V;   // where the last V entries begin
+    const bool few = last < rp[0];    // fewer entries than one load
     struct Entries {
         int32_t c[V];
         LenT l[V];
@@ -82,10 +84,14 @@ __global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, int64_t nnz,
         Entries e;
         int64_t at = 0;
         auto load = [&]() {  // V entries in one load each, from q or the last V of the array
-            at = q < nnz - V ? q : nnz - V;
+            at = q < last ? q : last;
             __builtin_memcpy(e.c, ci + at, sizeof(e.c));
             __builtin_memcpy(e.l, ln + at, sizeof(e.l));
         };
+        if (few) {
+            for (; lane % L == 0 && q < end; ++q) acc = fma((double)ln[q], x[ci[q]], acc);
+            q = end;
+        }
         if (q < end) load();
         while (q < end) {
             double f[V];
@@ -816,24 +822,21 @@ unsigned gather_blocks(int64_t groups)
 }
 
 template <typename LenT>
-int32_t gather_rows(int64_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const void* ln, const double* x,
-                    double* out, hipStream_t st)
+int32_t gather_rows(int64_t n, const int64_t* rp, const int32_t* ci, const void* ln, const double* x, double* out,
+                    hipStream_t st)
 {
     const unsigned blocks = gather_blocks((n + 7) / 8);
-    if (nnz >= 4)
-        row_gather_kernel<LenT, 4><<<blocks, 256, 0, st>>>(n, nnz, rp, ci, (const LenT*)ln, x, out);
-    else
-        row_gather_kernel<LenT, 1><<<blocks, 256, 0, st>>>(n, nnz, rp, ci, (const LenT*)ln, x, out);
+    row_gather_kernel<LenT><<<blocks, 256, 0, st>>>(n, rp, ci, (const LenT*)ln, x, out);
     PILA_HIP(hipGetLastError());
     return PILA_OK;
 }
 
-int32_t gather_rows(int32_t len_dtype, int64_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const void* ln,
-                    const double* x, double* out, hipStream_t st)
+int32_t gather_rows(int32_t len_dtype, int64_t n, const int64_t* rp, const int32_t* ci, const void* ln, const double* x,
+                    double* out, hipStream_t st)
 {
-    if (len_dtype == PILA_F64) return gather_rows<double>(n, nnz, rp, ci, ln, x, out, st);
-    if (len_dtype == PILA_F32) return gather_rows<float>(n, nnz, rp, ci, ln, x, out, st);
-    return gather_rows<LenQ>(n, nnz, rp, ci, ln, x, out, st);
+    if (len_dtype == PILA_F64) return gather_rows<double>(n, rp, ci, ln, x, out, st);
+    if (len_dtype == PILA_F32) return gather_rows<float>(n, rp, ci, ln, x, out, st);
+    return gather_rows<LenQ>(n, rp, ci, ln, x, out, st);
 }
 
 int32_t check_csr(const pila_geom* g, const pila_csr* c, bool need_rays, bool need_pixels)
@@ -859,8 +862,8 @@ extern "C" int32_t pila_forward(const pila_geom* geom, const pila_csr* csr, cons
     clear_error();
     PILA_TRY(check_csr(geom, csr, true, false));
     if (!d_image || !d_out) return fail(PILA_EINVAL, "image or output is NULL");
-    return gather_rows(geom->len_dtype, (int64_t)geom->n_angles * geom->n_bins, csr->nnz, csr->t_row_ptr, csr->t_col,
-                       csr->t_len, d_image, d_out, (hipStream_t)stream);
+    return gather_rows(geom->len_dtype, (int64_t)geom->n_angles * geom->n_bins, csr->t_row_ptr, csr->t_col, csr->t_len,
+                       d_image, d_out, (hipStream_t)stream);
 }
 
 extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, const double* d_sino,
@@ -869,7 +872,7 @@ extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, 
     clear_error();
     PILA_TRY(check_csr(geom, csr, false, true));
     if (!d_sino || !d_out) return fail(PILA_EINVAL, "sinogram or output is NULL");
-    return gather_rows(geom->len_dtype, (int64_t)geom->n * geom->n, csr->nnz, csr->row_ptr, csr->col, csr->len, d_sino, d_out,
+    return gather_rows(geom->len_dtype, (int64_t)geom->n * geom->n, csr->row_ptr, csr->col, csr->len, d_sino, d_out,
                        (hipStream_t)stream);
 }
 
