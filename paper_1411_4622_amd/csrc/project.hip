@@ -45,9 +45,9 @@ __device__ __forceinline__ XcdRows xcd_rows(int64_t n, int w)
 }
 
 // out[g] = sum over CSR row g of length times x[index] (FP64, fused
-// multiply-add).  A wavefront takes 8 neighbouring rows, 8 lanes each, and a
-// lane V consecutive entries at a time: lane e of a row the entries
-// e V + 8 V i .. + V - 1 by ascending i; its sum is added to the other
+// multiply-add).  A wavefront takes R neighbouring rows, L = 64 / R lanes each,
+// and a lane V consecutive entries at a time: lane e of a row the entries
+// e V + L V i .. + V - 1 by ascending i; its sum is added to the other
 // lanes' by a butterfly.  A row's consecutive entries lie on a line of x
 // each (a pixel's on another sinogram row per angle, a steep ray's on another
 // image row each), while neighbouring rows' entries lie on the same lines, so
@@ -56,16 +56,16 @@ __device__ __forceinline__ XcdRows xcd_rows(int64_t n, int w)
 // accesses of a CU's address path that bound this kernel.  The next entries
 // are loaded while the gathers are in flight.
 // 1024 x 1024, 720 angles, FP32 (7.6e8 entries, 6 GB; one access a lane alone
-// would be 1.3 ms): forward 4.05 -> 2.11 ms, back 4.85 -> 2.66 ms; 256 x 256 x
-// 180: 45 -> 31 and 56 -> 31 us.  (Eight rows at once but 64 lanes on each:
-// 2.41 and 2.94 ms.)
-template <typename LenT>
+// would be 1.3 ms), R = 8: forward 4.05 -> 2.11 ms, back 4.85 -> 2.66 ms; 256 x
+// 256 x 180: 45 -> 31 and 56 -> 31 us.  (Eight rows at once but 64 lanes on
+// each: 2.41 and 2.94 ms.)
+template <typename LenT, int R>
 __global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, const int64_t* __restrict__ rp,
                                                          const int32_t* __restrict__ ci,
                                                          const LenT* __restrict__ ln,
                                                          const double* __restrict__ x, double* __restrict__ out)
 {
-    constexpr int R = 8, L = 64 / R, V = 4;
+    constexpr int L = 64 / R, V = 4;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const XcdRows xr = xcd_rows<R>(n, w);
@@ -116,6 +116,41 @@ __global__ __launch_bounds__(256) void row_gather_kernel(int64_t n, const int64_
 #pragma unroll
         for (int s = 1; s < L; s <<= 1) acc += __shfl_xor(acc, s, 64);
         if (on && lane % L == 0) out[row] = acc;
+    }
+}
+
+// The same sum by one wavefront a row, 64 entries at a time and kU of these in
+// flight, for a few long rows, where the latency of a row's walk is what counts:
+// 64 rows of 5100 entries 10 us (two rows a wavefront 26 to 33).
+template <typename LenT>
+__global__ __launch_bounds__(256) void row_gather_one_kernel(int64_t n, const int64_t* __restrict__ rp,
+                                                             const int32_t* __restrict__ ci,
+                                                             const LenT* __restrict__ ln,
+                                                             const double* __restrict__ x, double* __restrict__ out)
+{
+    constexpr int kU = 8;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const XcdRows xr = xcd_rows<1>(n, w);
+    for (int64_t g = xr.first; g < xr.end; g += xr.stride) {
+        const int64_t b = rp[g], e = rp[g + 1];
+        double acc = 0.0;
+        for (int64_t q0 = b + lane; q0 < e; q0 += 64 * kU) {
+            int32_t c[kU];
+            double l[kU], v[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t q = q0 + 64 * u < e ? q0 + 64 * u : b;
+                c[u] = ci[q];
+                l[u] = (double)ln[q];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) v[u] = x[c[u]];
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (q0 + 64 * u < e) acc = fma(l[u], v[u], acc);
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) out[g] = acc;
     }
 }
 
@@ -821,22 +856,47 @@ unsigned gather_blocks(int64_t groups)
     return (unsigned)((b + 7) / 8 * 8);  // a multiple of the 8 XCDs, at least 8
 }
 
-template <typename LenT>
-int32_t gather_rows(int64_t n, const int64_t* rp, const int32_t* ci, const void* ln, const double* x, double* out,
-                    hipStream_t st)
+// Rows a wavefront takes at once.  More rows share more lines of x, fewer have
+// more wavefronts and more of a row in flight: with n rows that reach across
+// `reach` steps (a ray the image's rows or columns, a pixel the angles), eight
+// only where they fill the GPU or the rows are short.  Measured (f32 and f64,
+// us, 8 / 4 / 2 / 1 rows): rays of 1024 x 1024, 1 angle 24 / 13 / 9 / 8; 6
+// angles 35 / 22 / 27 / 30; 512 x 512, 16 angles 19 / 12 / 14 / 16; 2048 x
+// 2048, 1 angle 54 / 26 / 31 / 30; pixels of 64 x 64, 720 angles 18 / 12 / 9 /
+// 11; 16 x 16, 5000 angles 86 / 50 / 30 / 13; rays of 128 x 128, 90 angles (16380
+// rows of 90 entries) 8 whatever is taken, of 64 x 64, 720 angles 8 / 9 / 12 / 15.
+int rows_per_wave(int64_t n, int64_t reach)
 {
-    const unsigned blocks = gather_blocks((n + 7) / 8);
-    row_gather_kernel<LenT><<<blocks, 256, 0, st>>>(n, rp, ci, (const LenT*)ln, x, out);
+    if (n >= 32768 || reach <= 128) return 8;
+    if (n >= 8192 || (n >= 2048 && reach >= 2048)) return 4;
+    return n >= 1024 ? 2 : 1;
+}
+
+template <typename LenT>
+int32_t gather_rows(int64_t n, int64_t reach, const int64_t* rp, const int32_t* ci, const void* ln, const double* x,
+                    double* out, hipStream_t st)
+{
+    const int R = rows_per_wave(n, reach);
+    const unsigned blocks = gather_blocks((n + R - 1) / R);
+    const LenT* l = (const LenT*)ln;
+    if (R == 8)
+        row_gather_kernel<LenT, 8><<<blocks, 256, 0, st>>>(n, rp, ci, l, x, out);
+    else if (R == 4)
+        row_gather_kernel<LenT, 4><<<blocks, 256, 0, st>>>(n, rp, ci, l, x, out);
+    else if (R == 2)
+        row_gather_kernel<LenT, 2><<<blocks, 256, 0, st>>>(n, rp, ci, l, x, out);
+    else
+        row_gather_one_kernel<LenT><<<blocks, 256, 0, st>>>(n, rp, ci, l, x, out);
     PILA_HIP(hipGetLastError());
     return PILA_OK;
 }
 
-int32_t gather_rows(int32_t len_dtype, int64_t n, const int64_t* rp, const int32_t* ci, const void* ln, const double* x,
-                    double* out, hipStream_t st)
+int32_t gather_rows(int32_t len_dtype, int64_t n, int64_t reach, const int64_t* rp, const int32_t* ci, const void* ln,
+                    const double* x, double* out, hipStream_t st)
 {
-    if (len_dtype == PILA_F64) return gather_rows<double>(n, rp, ci, ln, x, out, st);
-    if (len_dtype == PILA_F32) return gather_rows<float>(n, rp, ci, ln, x, out, st);
-    return gather_rows<LenQ>(n, rp, ci, ln, x, out, st);
+    if (len_dtype == PILA_F64) return gather_rows<double>(n, reach, rp, ci, ln, x, out, st);
+    if (len_dtype == PILA_F32) return gather_rows<float>(n, reach, rp, ci, ln, x, out, st);
+    return gather_rows<LenQ>(n, reach, rp, ci, ln, x, out, st);
 }
 
 int32_t check_csr(const pila_geom* g, const pila_csr* c, bool need_rays, bool need_pixels)
@@ -862,8 +922,8 @@ extern "C" int32_t pila_forward(const pila_geom* geom, const pila_csr* csr, cons
     clear_error();
     PILA_TRY(check_csr(geom, csr, true, false));
     if (!d_image || !d_out) return fail(PILA_EINVAL, "image or output is NULL");
-    return gather_rows(geom->len_dtype, (int64_t)geom->n_angles * geom->n_bins, csr->t_row_ptr, csr->t_col, csr->t_len,
-                       d_image, d_out, (hipStream_t)stream);
+    return gather_rows(geom->len_dtype, (int64_t)geom->n_angles * geom->n_bins, geom->n, csr->t_row_ptr, csr->t_col,
+                       csr->t_len, d_image, d_out, (hipStream_t)stream);
 }
 
 extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, const double* d_sino,
@@ -872,8 +932,8 @@ extern "C" int32_t pila_backproject(const pila_geom* geom, const pila_csr* csr, 
     clear_error();
     PILA_TRY(check_csr(geom, csr, false, true));
     if (!d_sino || !d_out) return fail(PILA_EINVAL, "sinogram or output is NULL");
-    return gather_rows(geom->len_dtype, (int64_t)geom->n * geom->n, csr->row_ptr, csr->col, csr->len, d_sino, d_out,
-                       (hipStream_t)stream);
+    return gather_rows(geom->len_dtype, (int64_t)geom->n * geom->n, geom->n_angles, csr->row_ptr, csr->col, csr->len,
+                       d_sino, d_out, (hipStream_t)stream);
 }
 
 extern "C" int32_t sirt_workspace_size(const pila_geom* geom, const sirt_params* params, size_t* bytes)
