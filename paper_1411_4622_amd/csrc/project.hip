@@ -242,9 +242,15 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ partial,
 constexpr int kTile = 8;
 constexpr int kOdd = -2;  // flag of a tile summed from its CSR rows
 
+// A tile's lengths have 128 places a step; those of kChunk steps are packed
+// together from the chunk's first place on, so that a position in the chunk and
+// its byte offset fit in 32 bits whatever the number of angles (a tile of 8 x 8
+// pixels under 7 million angles has more than 4 GiB of lengths).
+constexpr int kChunk = 1 << 21;
+
 struct StepHead {
     uint64_t m0, m1;  // lanes with an entry at b, at b + 1
-    int32_t pos, pad; // the step's first length in its tile's array
+    int32_t pos, pad; // the step's first length among its chunk's
 };
 
 __device__ __forceinline__ int64_t tile_pixel(const int32_t* tiles, int t, int lane, int N)
@@ -335,7 +341,8 @@ struct LayoutLds {
     int row_n[64];
     int off[kSpan + 1];
     int taken[2][64];  // per row: entries before its first one not taken, this span's and the next's
-    int bad, entries;
+    int bad;
+    unsigned long long entries;
 };
 
 // steps of one entry: the step it belongs to and its index in the step's line
@@ -360,7 +367,8 @@ __device__ __forceinline__ void place(LayoutLds<LenT>& L, int x, int slot, int r
     L.stage[L.off[x] + __popcll(m0 & below) + __popcll(m1 & below) + mine] = l;
 }
 
-// after the span's masks: its steps' places and heads; `total` lengths precede
+// after the span's masks: its steps' places and heads; `total` lengths of the
+// chunk precede
 template <typename LenT>
 __device__ __forceinline__ void layout_places(LayoutLds<LenT>& L, StepHead* head, int x0, int steps, int total, int lane,
                                               int w, int* first, int* last)
@@ -470,13 +478,19 @@ __global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, i
         L.row_b[tid] = n > 0 ? b : 0;
         L.row_n[tid] = n;
         L.taken[0][tid] = 0;
-        if (n > 0) atomicAdd(&L.entries, n);
+        if (n > 0) atomicAdd(&L.entries, (unsigned long long)n);
     }
     int total = 0, first = steps, last = -1;
+    unsigned long long placed = 0;  // in earlier chunks
     for (int sp = 0; sp < spans; ++sp) {
         const int x0 = (down ? spans - 1 - sp : sp) * kSpan;
         const int x1 = x0 + kSpan < steps ? x0 + kSpan : steps;
         const int now = sp & 1;
+        if (!RAY && x0 > 0 && x0 % kChunk == 0) {  // (an image has fewer rows than a chunk)
+            placed += (unsigned)total;
+            total = 0;
+            out += (int64_t)kChunk * 128;
+        }
         if (tid < 2 * kSpan) L.mask[tid / kSpan][tid % kSpan] = 0;
         __syncthreads();
         if constexpr (down) {
@@ -545,7 +559,7 @@ __global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, i
         __syncthreads();
     }
     if (tid == 0) {
-        const bool odd = L.bad || total != L.entries;
+        const bool odd = L.bad || placed + (unsigned)total != L.entries;
         if (RAY) {
             flag[2 * t] = odd ? 0 : first;
             flag[2 * t + 1] = odd ? kOdd : last;
@@ -615,14 +629,13 @@ __device__ __forceinline__ double tile_steps(double acc, int s0, int line, const
     return acc;
 }
 
-// Sum over the steps lo..hi of one lane's entries: length times src[step line
-// + b (+ 1)], by ascending step, b before b + 1.
+// acc plus the sum over the steps lo..hi, of one chunk, of one lane's entries:
+// length times src[step line + b (+ 1)], by ascending step, b before b + 1.
 template <typename LenT, int S, typename Row>
-__device__ __forceinline__ double tile_sum(int lo, int hi, int line, const Row& row, const double* __restrict__ trig,
-                                           const StepHead* __restrict__ head, const LenT* __restrict__ lens,
+__device__ __forceinline__ double tile_sum(double acc, int lo, int hi, int line, const Row& row,
+                                           const double* __restrict__ trig, const StepHead* __restrict__ head, const LenT* __restrict__ lens,
                                            const double* __restrict__ src)
 {
-    double acc = 0.0;
     int s = lo;
     for (; s + S - 1 <= hi; s += S) acc = tile_steps<LenT, S>(acc, s, line, row, trig, head, lens, src);
     for (; s <= hi; ++s) acc = tile_steps<LenT, 1>(acc, s, line, row, trig, head, lens, src);
@@ -692,7 +705,10 @@ __global__ __launch_bounds__(256) void tile_back_kernel(int N, int U, int K, int
         int a, b;
         wave_part(0, U - 1, w, &a, &b);
         const PixelRow row(N, K, p);
-        acc = tile_sum<LenT, kA>(a, b, K, row, trig, heads + t * U, lens + t * U * 128, y);
+        const LenT* l = lens + t * U * 128;
+        for (; a <= b; a = (a | (kChunk - 1)) + 1)
+            acc = tile_sum<LenT, kA>(acc, a, min(b, a | (kChunk - 1)), K, row, trig, heads + t * U,
+                                     l + (int64_t)(a & ~(kChunk - 1)) * 128, y);
     }
     part[w][lane] = acc;
     __syncthreads();
@@ -758,7 +774,7 @@ __global__ __launch_bounds__(64) void ray_tile_part_kernel(int N, int K, int nkt
         const int b0 = (int)bnd * band;
         const int a = lo > b0 ? lo : b0, b = hi < b0 + band - 1 ? hi : b0 + band - 1;
         const RayRow row(N, K, trig, u, k);
-        acc = tile_sum<LenT, kS>(a, b, N, row, trig, heads + t * N, lens + t * N * 128, img);
+        acc = tile_sum<LenT, kS>(0.0, a, b, N, row, trig, heads + t * N, lens + t * N * 128, img);
     }
     part[(bnd * n_tiles + t) * 64 + lane] = acc;
 }
