@@ -58,6 +58,17 @@ int32_t check_geom(const pila_geom* g);
 // host: bytes of one stored length of a len_dtype
 inline int len_bytes(int32_t dtype) { return dtype == PILA_F64 ? 8 : dtype == PILA_F32 ? 4 : 1; }
 
+// Launches of more workgroups than one grid dimension takes (2^32 threads; more
+// are dropped without an error): the workgroups in rows of kGridRow, the last
+// row padded, and a workgroup's number.
+constexpr unsigned kGridRow = 1u << 21;
+inline dim3 grid_of(int64_t blocks)
+{
+    return blocks <= (int64_t)kGridRow ? dim3((unsigned)blocks)
+                                       : dim3(kGridRow, (unsigned)((blocks + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ unsigned block_of() { return blockIdx.y * kGridRow + blockIdx.x; }
+
 // ---------------------------------------------------------------------------
 // device: Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11)
 // ---------------------------------------------------------------------------

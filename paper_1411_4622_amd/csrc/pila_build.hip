@@ -338,9 +338,11 @@ __global__ __launch_bounds__(kCountThreads, 8) void count_kernel(int32_t N, int3
     __shared__ int part[kParts][kScanChunk];
     __shared__ int wsum[kScanChunk / kWave];
     const int t = threadIdx.x, lane = t & (kWave - 1);
-    const bool px = blockIdx.x < pixel_blocks;
+    const unsigned block = block_of();
+    const bool px = block < pixel_blocks;
     const int64_t n = px ? (int64_t)N * N : (int64_t)U * K;
-    const int64_t first = (int64_t)(px ? blockIdx.x : blockIdx.x - pixel_blocks) * kScanChunk;
+    const int64_t first = (int64_t)(px ? block : block - pixel_blocks) * kScanChunk;
+    if (first >= n) return;  // the grid's padding
     const int w = __builtin_amdgcn_readfirstlane(t / kScanChunk);
     const int64_t at = first + t % kScanChunk;
     int mine = 0;
@@ -481,7 +483,7 @@ __global__ __launch_bounds__(256) void pixel_fill_kernel(int32_t N, int32_t U, i
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_row = (N + kPix - 1) / kPix;
-    const int64_t grp = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    const int64_t grp = (int64_t)block_of() * kWavesPerBlock + wave;
     if (grp >= (int64_t)N * per_row || row_ptr[(int64_t)N * N] != nnz) return;
     const int i = (int)(grp / per_row), j0 = (int)(grp - (int64_t)i * per_row) * kPix;
     const double hc = 0.5 * N - 0.5, cK = 0.5 * (K - 1);
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(256) void ray_fill_kernel(int32_t N, int32_t U, int
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t G = (int64_t)U * K;
-    const int64_t g = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    const int64_t g = (int64_t)block_of() * kWavesPerBlock + wave;
     if (g >= G || t_row_ptr[G] != nnz) return;
     int64_t q = t_row_ptr[g];
     if (t_row_ptr[g + 1] == q) return;
@@ -716,9 +718,9 @@ template <typename LenT>
 void launch_fill(const pila_geom* g, pila_csr* csr, const MaskView& mv, hipStream_t st)
 {
     const int64_t groups = (int64_t)g->n * ((g->n + kPix - 1) / kPix), G = (int64_t)g->n_angles * g->n_bins;
-    pixel_fill_kernel<LenT><<<blocks_of(groups, kWavesPerBlock), 256, 0, st>>>(
+    pixel_fill_kernel<LenT><<<grid_of(blocks_of(groups, kWavesPerBlock)), 256, 0, st>>>(
         g->n, g->n_angles, g->n_bins, csr->nnz, csr->trig, csr->row_ptr, csr->col, (LenT*)csr->len);
-    ray_fill_kernel<LenT><<<blocks_of(G, kWavesPerBlock), 256, 0, st>>>(
+    ray_fill_kernel<LenT><<<grid_of(blocks_of(G, kWavesPerBlock)), 256, 0, st>>>(
         g->n, g->n_angles, g->n_bins, csr->nnz, csr->trig, mv, csr->t_row_ptr, csr->t_col, (LenT*)csr->t_len);
 }
 
@@ -780,8 +782,8 @@ int32_t pila::pila_build_with(const pila_geom* geom, pila_csr* csr, void* d_scra
                                 hipMemcpyHostToDevice, st));
         const unsigned pb = blocks_of(NP, kScanChunk), rb = blocks_of(G, kScanChunk);
         int64_t* d_res = (int64_t*)d_scratch;  // entries by pixel, entries by ray, longest pixel row
-        count_kernel<<<pb + rb, kCountThreads, 0, st>>>(N, U, K, csr->trig, mv, pb, csr->row_ptr, csr->t_row_ptr,
-                                                        d_res + 2);
+        count_kernel<<<grid_of((int64_t)pb + rb), kCountThreads, 0, st>>>(N, U, K, csr->trig, mv, pb, csr->row_ptr,
+                                                                         csr->t_row_ptr, d_res + 2);
         PILA_HIP(hipGetLastError());
         chunk_scan_kernel<<<2, 1024, 0, st>>>(csr->row_ptr, NP, csr->t_row_ptr, G, d_res);
         chunk_add_kernel<<<pb + rb, kScanChunk, 0, st>>>(csr->row_ptr, NP, pb, csr->t_row_ptr, G);

@@ -434,7 +434,7 @@ __device__ __forceinline__ void layout_span_down(LayoutLds<LenT>& L, const Entry
 }
 
 template <typename LenT, int MODE>
-__global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, int nkt, int64_t nnz,
+__global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, int nkt, int n_tiles, int64_t nnz,
                                                          const double* __restrict__ trig,
                                                          const int32_t* __restrict__ tiles,
                                                          const int64_t* __restrict__ rp,
@@ -448,7 +448,8 @@ __global__ __launch_bounds__(256) void tile_layout_kernel(int N, int U, int K, i
     // rows of a wavefront; windows of 64 entries a span
     constexpr int kRows = 16, kW = 2 * kSpan / 64 + (MODE == kRayDown ? 1 : 0);
     __shared__ LayoutLds<LenT> L;
-    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int t = (int)block_of(), tid = threadIdx.x, lane = tid & 63;
+    if (t >= n_tiles) return;  // the grid's padding
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int steps = RAY ? N : U;
     const int u = RAY ? t / nkt : 0, k0 = RAY ? (t - u * nkt) * 64 : 0;
@@ -633,8 +634,8 @@ __device__ __forceinline__ double tile_steps(double acc, int s0, int line, const
 // length times src[step line + b (+ 1)], by ascending step, b before b + 1.
 template <typename LenT, int S, typename Row>
 __device__ __forceinline__ double tile_sum(double acc, int lo, int hi, int line, const Row& row,
-                                           const double* __restrict__ trig, const StepHead* __restrict__ head, const LenT* __restrict__ lens,
-                                           const double* __restrict__ src)
+                                           const double* __restrict__ trig, const StepHead* __restrict__ head,
+                                           const LenT* __restrict__ lens, const double* __restrict__ src)
 {
     int s = lo;
     for (; s + S - 1 <= hi; s += S) acc = tile_steps<LenT, S>(acc, s, line, row, trig, head, lens, src);
@@ -992,9 +993,10 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     if (n_tiles > 0 && !reuse) {
         PILA_HIP(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int32_t) * tiles.size(),
                                 hipMemcpyHostToDevice, st));
-        tile_layout_kernel<LenT, kPixels><<<n_tiles, 256, 0, st>>>(N, U, K, 0, csr->nnz, csr->trig, d_tiles, csr->row_ptr,
-                                                                 csr->col, (const LenT*)csr->len, heads, lens, flag,
-                                                                 force_csr);
+        tile_layout_kernel<LenT, kPixels><<<grid_of(n_tiles), 256, 0, st>>>(N, U, K, 0, n_tiles, csr->nnz, csr->trig,
+                                                                          d_tiles, csr->row_ptr, csr->col,
+                                                                          (const LenT*)csr->len, heads, lens, flag,
+                                                                          force_csr);
     }
     const int nkt = (K + 63) / 64, n_rt = U * nkt;
     StepHead* rheads = (StepHead*)(ws + L.rheads);
@@ -1003,10 +1005,10 @@ static int32_t sirt_impl(const pila_geom* geom, const pila_csr* csr, const doubl
     double* bpart = (double*)(ws + L.bpart);
     const int band = ray_band(N, n_rt), n_bands = (N + band - 1) / band;
     if (!reuse) {
-        tile_layout_kernel<LenT, kRayUp><<<n_rt, 256, 0, st>>>(N, U, K, nkt, csr->nnz, csr->trig, nullptr,
+        tile_layout_kernel<LenT, kRayUp><<<grid_of(n_rt), 256, 0, st>>>(N, U, K, nkt, n_rt, csr->nnz, csr->trig, nullptr,
                                                               csr->t_row_ptr, csr->t_col, (const LenT*)csr->t_len,
                                                               rheads, rlens, range, force_csr);
-        tile_layout_kernel<LenT, kRayDown><<<n_rt, 256, 0, st>>>(N, U, K, nkt, csr->nnz, csr->trig, nullptr,
+        tile_layout_kernel<LenT, kRayDown><<<grid_of(n_rt), 256, 0, st>>>(N, U, K, nkt, n_rt, csr->nnz, csr->trig, nullptr,
                                                                 csr->t_row_ptr, csr->t_col, (const LenT*)csr->t_len,
                                                                 rheads, rlens, range, force_csr);
     }
