@@ -460,11 +460,12 @@ struct Schedule {
     // (stage + 1) n_steps = n_stages whole + rest; per stage they grow by the
     // quotient and remainder of n_steps / n_stages, so that no step divides
     int64_t whole, quot;
-    int32_t rest, rem, n_stages;
+    uint32_t rest, rem;  // (below n_stages, so their sum fits)
+    int32_t n_stages;
     double T0, TN, dT, NN;
     int kind;
     double T, invT;  // temperature of the current stage and its reciprocal
-    __device__ void start(int64_t s, int64_t n_steps, int32_t stages, double t0, double tn, int k)
+    __host__ __device__ void start(int64_t s, int64_t n_steps, int32_t stages, double t0, double tn, int k)
     {
         T0 = t0;
         TN = tn;
@@ -474,13 +475,13 @@ struct Schedule {
         dT = (t0 - tn) / NN;
         stage = n_steps > 0 ? (s * (int64_t)n_stages) / n_steps : 0;
         quot = n_steps / n_stages;
-        rem = (int32_t)(n_steps - quot * n_stages);
+        rem = (uint32_t)(n_steps - quot * n_stages);
         whole = ((stage + 1) * n_steps) / n_stages;
-        rest = (int32_t)((stage + 1) * n_steps - whole * n_stages);
+        rest = (uint32_t)((stage + 1) * n_steps - whole * n_stages);
         next = whole + (rest > 0 ? 1 : 0);
         set();
     }
-    __device__ void set()
+    __host__ __device__ void set()
     {
         const double x = (double)stage;
         if (kind == PILA_SCHED_EXP)
@@ -491,15 +492,15 @@ struct Schedule {
             T = T0 - x * dT;
         invT = 1.0 / T;
     }
-    __device__ double at(int64_t s)
+    __host__ __device__ double at(int64_t s)
     {
         if (__builtin_expect(s >= next, 0)) {
             while (s >= next) {
                 ++stage;
                 whole += quot;
                 rest += rem;
-                if (rest >= n_stages) {
-                    rest -= n_stages;
+                if (rest >= (uint32_t)n_stages) {
+                    rest -= (uint32_t)n_stages;
                     ++whole;
                 }
                 next = whole + (rest > 0 ? 1 : 0);
