@@ -138,6 +138,14 @@ int device_props(hipDeviceProp_t* prop)
     return PILA_OK;
 }
 
+bool ahead_allowed(const sat_params* p)
+{
+    // redrawn proposals depend on the image value at the step, and blocks of
+    // 16 to 64 steps are numbered in 32 bits (a chain of more than 2^34 steps
+    // would run for hours on end before it got there)
+    return p->proposal == PILA_PROP_CLAMP && p->n_steps <= (int64_t)1 << 34;
+}
+
 bool piped_allowed(const pila_geom* g, const pila_csr* c)
 {
     // ray index g = u K + k below 2^24 (the multiply-shift split), bins
@@ -770,8 +778,7 @@ static int32_t sat_run_impl(const pila_geom* geom, const pila_csr* csr, const do
     const bool r_in_lds = G * rs <= budget;
     const int table_lds = (int)hybrid_lds(&J, budget);
     int waves = 0;
-    // redrawn proposals depend on the image value at the step: general body only
-    const bool ahead = params->proposal == PILA_PROP_CLAMP;
+    const bool ahead = ahead_allowed(params);
     const bool lenq = J.lenq != 0;
     const PipedShape* ps = ahead && piped_allowed(geom, csr)
                                ? choose_piped(params->precision, lenq, params->m_cand, csr->max_row, &waves)
@@ -1133,7 +1140,7 @@ static int32_t batch_plan(int32_t n_jobs, const sat_job* jobs, const sat_launch*
     for (int32_t j = 0; j < n_jobs; ++j) {
         ChainJob& J = host[j];
         const int waves = jobs[j].waves_per_chain ? jobs[j].waves_per_chain : launch_waves;
-        const bool ahead = J.proposal == PILA_PROP_CLAMP;
+        const bool ahead = ahead_allowed(&jobs[j].params);
         const bool fits = ahead && waves * kWave <= kPipedThreads;
         const BatchShape* bs = nullptr;
         if (fits && piped_allowed(jobs[j].geom, jobs[j].csr) && jobs[j].geom->n_angles <= kSlotMaxAngles) {

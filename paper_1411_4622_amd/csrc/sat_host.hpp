@@ -17,6 +17,9 @@ int32_t check_params(const pila_geom* g, const pila_csr* c, const sat_params* p)
 ChainJob make_job(const pila_geom* g, const pila_csr* c, const double* sino, const sat_params* p,
                   double* image, char* ws);
 int device_props(hipDeviceProp_t* prop);
+// whether the pipelined and long-row bodies, which draw a block of steps ahead,
+// can take a chain (the general and split bodies take any)
+bool ahead_allowed(const sat_params* p);
 // whether the pipelined body's index arithmetic holds for this PILA
 bool piped_allowed(const pila_geom* g, const pila_csr* c);
 // LDS bytes of a pipelined chain with the residual partly in LDS; sets J->UL

@@ -681,8 +681,7 @@ extern "C" int32_t srv_submit(srv_t* s, const srv_request* req, uint64_t* ticket
     // long-row body for longer rows, else the general body
     const RingShape* ps = s->q[kPiped].shape;
     ChainJob probe = make_job(&e->geom, &e->csr, req->d_sino, &req->params, req->d_image, nullptr);
-    // redrawn proposals depend on the image value at the step: general body only
-    const bool f32 = req->params.precision == PILA_F32 && req->params.proposal == PILA_PROP_CLAMP;
+    const bool f32 = req->params.precision == PILA_F32 && ahead_allowed(&req->params);
     int qi = kGeneral;
     if (f32 && e->tcol && piped_allowed(&e->geom, &e->csr) && req->params.m_cand <= ps->waves * ps->cpw &&
         e->csr.max_row <= (kWave / ps->cpw) * ps->e && hybrid_lds(&probe, s->lds_bytes) <= s->lds_bytes)
