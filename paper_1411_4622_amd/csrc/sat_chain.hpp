@@ -895,7 +895,10 @@ __device__ __forceinline__ bool accepts(double dC, double T, double invT, double
 // what the answer needs is formed: a change that does not raise the sum is
 // accepted by its sign; one that does is first estimated in FP32 (one
 // hardware square root per term and a reciprocal, relative error below 1e-6
-// over the checked range) and settled by it when -dC / T and ln N1 differ by
+// over the checked range: there the quotient is a normal number, and a total
+// too small to be one adds less than 1.1e-19 to a denominator above 1e-12; a
+// 1 / T too small to be one leaves -dC / T far below any ln N1, and one too large
+// is settled in FP64) and settled by it when -dC / T and ln N1 differ by
 // more than 4e-6 relative; the FP64 square roots and divisions of Eq. 7 run
 // only inside that band.  (With both square roots and three divisions formed
 // for every lane the decision took 1200 clocks of a step, then 640: 64 x 64,
@@ -922,7 +925,7 @@ __device__ __forceinline__ Decision decide(double S, int M, int lane, double sse
     }
     if (__builtin_expect(finite, 1)) {
         const float n = (float)(dn.S * invKU), b = (float)(sse * invKU), a = (float)((sse + dn.S) * invKU);
-        if (__builtin_expect(n > 1e-30f && a < 1e30f, 1)) {
+        if (__builtin_expect(n > 1e-24f && a < 1e24f, 1)) {
             const float den = __builtin_amdgcn_sqrtf(a) + __builtin_amdgcn_sqrtf(b);
             const float x = -n * __builtin_amdgcn_rcpf(den) * (float)invT, y = (float)lnN1;
             const float margin = 4e-6f * (fabsf(x) + fabsf(y));
