@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kPipedThreads) void sat_piped_kernel(ChainJob job)
 {
     extern __shared__ __align__(16) char lds[];
     __shared__ ChainShared sh;
-    run_chain_piped<Real, RLDS, CPW, E, false, TK, LenT, true>(job, lds, sh, false);
+    run_chain_piped<Real, RLDS, CPW, E, false, TK, LenT, true, !TK && sizeof(Real) == 4>(job, lds, sh, false);
 }
 
 // one segment of a chain whose FP64 resyncs run grid-wide between segments

@@ -1664,7 +1664,7 @@ __device__ void lds_residual_store(const ChainJob& J, Real* r, const Real* rl)
 // otherwise at the load (batches, where the compiler places that better).
 // Either way the same float results.
 template <typename Real, bool RLDS, int CPW, int E, bool SERVED = false, bool TK = false, typename LenT = Real,
-          bool LATE = false>
+          bool LATE = false, bool EARLY = false>
 __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, bool segmented)
 {
     constexpr int LPC = kWave / CPW;  // lanes per estimate
@@ -1676,8 +1676,11 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
     // it is used (256 x 256, 180 angles, M = 16, FP32: 51.1 to 48.7 ms).  One
     // estimate a wavefront: the owner's longer writes and the row loads then
     // add up (a batch of 32 chains: 318 to 330 ms), so it is asked for before
-    // the step's first barrier.
-    constexpr bool kRowsLate = CPW > 1 && !RLDS;
+    // the step's first barrier.  EARLY: before the barrier for several estimates
+    // too; the lone FP32 kernels without slot words run out of registers
+    // otherwise (290 spilled; 256 x 256, 180 angles, M = 16, 10000 steps: 54.5
+    // against 32.1 ms; the segment kernels do not, and take 29.5 against 31.3).
+    constexpr bool kRowsLate = CPW > 1 && !RLDS && !EARLY;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
     const int slot = lane / LPC, li = lane % LPC;
     const double KU = (double)J.K * (double)J.U;
