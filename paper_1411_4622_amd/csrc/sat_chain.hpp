@@ -108,6 +108,20 @@ __device__ __forceinline__ void stg(T* p, I i, T v)
         ((Global<T>*)p)[i] = v;
     }
 }
+// element i of a global array through a 32-bit byte offset from a uniform
+// base (one address register per load): of a row, or of a whole array, which
+// the host then keeps below 4 GiB
+template <typename T>
+__device__ __forceinline__ T ld32(const T* base, uint32_t i)
+{
+    return ldg((const T*)((const char*)base + i * (uint32_t)sizeof(T)), 0);
+}
+template <typename T>
+__device__ __forceinline__ void st32(T* base, uint32_t i, T v)
+{
+    stg((T*)((char*)base + i * (uint32_t)sizeof(T)), 0, v);
+}
+
 // a value of a residual that is in global memory (GLOB) or in LDS
 template <bool GLOB, typename T, typename I>
 __device__ __forceinline__ T ldr(const T* r, I i)
@@ -996,9 +1010,17 @@ __device__ __forceinline__ void resync_in_group(const ChainJob& J, ChainState& c
 
 // ---------------------------------------------------------------------------
 // any row length, any M
+//
+// Inlined into each kernel: as a function of its own, which is what the compiler
+// makes of it once several kernels call it, it reads the descriptor by flat loads
+// at every use, and each wait for one waits for the rows and residual values asked
+// for before it.  10000 steps, residual in LDS and in global memory: 64 x 64, 90
+// angles, M = 32, FP32 181 -> 76 ms; M = 64, FP64 228 -> 158; 400 x 400, 90 angles,
+// M = 32, FP32 187 -> 93, FP64 221 -> 115; 256 x 256, 180 angles, M = 8 redrawn, FP64
+// 110 -> 63.
 // ---------------------------------------------------------------------------
 template <typename Real, bool LDS, typename LenT = Real, bool SERVED = false>
-__device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, bool segmented = false)
+__device__ __forceinline__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, bool segmented = false)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
     const double KU = (double)J.K * (double)J.U;
@@ -1110,20 +1132,25 @@ __device__ void run_chain_simple(const ChainJob& J, char* lds, ChainShared& sh, 
                 }
             }
             const Real dra = (Real)dd[0], drb = (Real)dd[1];
-            const int64_t la = ee[0] - bb[0], lb = ee[1] - bb[1];
-            const int64_t lmax = la > lb ? la : lb;
+            // (a row by its uniform base and 32-bit offsets: an address per load
+            // takes twice the registers, which 16 wavefronts do not have)
+            const int64_t ba = uniform_i64(bb[0]), bb1 = uniform_i64(bb[1]);
+            const int la = uniform_i32((int)(ee[0] - bb[0])), lb = uniform_i32((int)(ee[1] - bb[1]));
+            const int lmax = la > lb ? la : lb;
+            const int32_t *cola = J.col.p + ba, *colb = J.col.p + bb1;
+            const LenT *lena = lenp + ba, *lenb = lenp + bb1;
             Real acca = 0, accb = 0;
-            for (int64_t o = lane; o < lmax; o += (int64_t)kWave * U) {
+            for (int o = lane; o < lmax; o += kWave * U) {
                 int32_t ca[U], cb[U];
                 Real la_[U], lb_[U];
 #pragma unroll
                 for (int c = 0; c < U; ++c) {
-                    const int64_t qa = bb[0] + (o + c * kWave < la ? o + c * kWave : 0);
-                    const int64_t qb = bb[1] + (o + c * kWave < lb ? o + c * kWave : 0);
-                    ca[c] = J.col[qa];
-                    la_[c] = (Real)ldg(lenp, qa);
-                    cb[c] = J.col[qb];
-                    lb_[c] = (Real)ldg(lenp, qb);
+                    const uint32_t qa = o + c * kWave < la ? (uint32_t)(o + c * kWave) : 0u;
+                    const uint32_t qb = o + c * kWave < lb ? (uint32_t)(o + c * kWave) : 0u;
+                    ca[c] = ld32(cola, qa);
+                    la_[c] = (Real)ld32(lena, qa);
+                    cb[c] = ld32(colb, qb);
+                    lb_[c] = (Real)ld32(lenb, qb);
                 }
                 Real ra[U], rb[U];
 #pragma unroll
@@ -1541,20 +1568,6 @@ __device__ void run_chain_split(const ChainJob& J, const SplitX& X, int g, Split
 // ---------------------------------------------------------------------------
 // pipelined: rows in registers two steps ahead, operands one step ahead
 // ---------------------------------------------------------------------------
-// element i of a global array through a 32-bit byte offset from a uniform
-// base (one address register per load); the host keeps every such array
-// below 4 GiB
-template <typename T>
-__device__ __forceinline__ T ld32(const T* base, uint32_t i)
-{
-    return ldg((const T*)((const char*)base + i * (uint32_t)sizeof(T)), 0);
-}
-template <typename T>
-__device__ __forceinline__ void st32(T* base, uint32_t i, T v)
-{
-    stg((T*)((char*)base + i * (uint32_t)sizeof(T)), 0, v);
-}
-
 // A length loaded a step or two before it is used: FP32 lengths as they are;
 // one-byte lengths as the raw byte in the register's bits, read back (q/180,
 // an ALU operation on the loaded value, len_use) once the load has arrived,
@@ -2285,7 +2298,7 @@ __device__ void run_chain_long(const ChainJob& J, char* lds, ChainShared& sh, bo
 }
 
 template <typename Real, typename LenT = Real, bool SERVED = false>
-__device__ void run_chain_simple_dispatch(const ChainJob& J, char* lds, int lds_bytes, ChainShared& sh)
+__device__ __forceinline__ void run_chain_simple_dispatch(const ChainJob& J, char* lds, int lds_bytes, ChainShared& sh)
 {
     if ((int64_t)J.U * J.K * (int64_t)sizeof(Real) <= lds_bytes)
         run_chain_simple<Real, true, LenT, SERVED>(J, lds, sh);
