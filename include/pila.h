@@ -198,10 +198,15 @@ typedef struct sat_stats {
                                per resync segment); 0 from sat_run_batch */
     int32_t body;           /* PILA_BODY_* kind | flags of the body that ran the chain */
     double chain_kernel_ms; /* sat_run: summed duration of those launches, from
-                               HIP events recorded around each of them */
+                               HIP events recorded around each of them (the
+                               first residual and the resyncs between segments
+                               are launches of their own, outside it) */
     int64_t t_begin, t_end; /* sat_run_batch and the server: device wall clock
                                (pila_device_info.wallclock_khz) when the chain's
-                               workgroup took it and when it finished; 0 from sat_run */
+                               workgroup took it and when it finished (a batch's
+                               first residuals are formed before, for all of its
+                               chains at once; a served chain's within); 0 from
+                               sat_run */
 } sat_stats;
 
 /* Optional per-step record, device arrays of n_steps elements (each may be

@@ -111,13 +111,6 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
-__device__ __forceinline__ int wave_isum(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
 // exclusive prefix over the lanes of a wave (lane order)
 __device__ __forceinline__ int wave_excl_scan(int v, int lane)
 {

@@ -336,7 +336,6 @@ __global__ __launch_bounds__(kCountThreads, 8) void count_kernel(int32_t N, int3
                                                               int64_t* __restrict__ max_row)
 {
     __shared__ int part[kParts][kScanChunk];
-    __shared__ int wsum[kScanChunk / kWave];
     const int t = threadIdx.x, lane = t & (kWave - 1);
     const unsigned block = block_of();
     const bool px = block < pixel_blocks;
@@ -358,19 +357,15 @@ __global__ __launch_bounds__(kCountThreads, 8) void count_kernel(int32_t N, int3
     }
     part[w][t % kScanChunk] = mine;
     __syncthreads();
-    int cnt = 0;
-    if (t < kScanChunk)
-        for (int q = 0; q < kParts; ++q) cnt += part[q][t];
-    const int sum = wave_excl_scan(cnt, lane) + cnt;
-    if (t < kScanChunk && lane == kWave - 1) wsum[t / kWave] = sum;
-    __syncthreads();
+    static_assert(kScanChunk == kWave, "the first wavefront scans the block's rows");
     if (t >= kScanChunk) return;
-    int pre = 0;
-    for (int q = 0; q < t / kWave; ++q) pre += wsum[q];
+    int cnt = 0;
+    for (int q = 0; q < kParts; ++q) cnt += part[q][t];
+    const int sum = wave_excl_scan(cnt, lane) + cnt;
     int64_t* out = px ? row_ptr : t_row_ptr;
     const int64_t x = first + t;
     if (x == 0) out[0] = 0;
-    if (x < n) out[x + 1] = pre + sum;
+    if (x < n) out[x + 1] = sum;
     if (px) {
         int m = cnt;
 #pragma unroll

@@ -7,8 +7,9 @@
 // back projection walks the pixel-major copy (a wavefront per few pixels).  Every
 // output is produced by exactly one wavefront in a fixed order, so results
 // are deterministic and need no atomics.  Both stream the PILA from HBM
-// once per call (the image / sinogram being gathered stays in L2 / MALL):
-// these are HBM-bound kernels.
+// once per call (the image / sinogram being gathered stays in L2 / MALL); what
+// bounds them at large sizes is the gathers, the accesses of a compute unit's
+// address path, at about half of HBM's rate (row_gather_kernel).
 #include <cmath>
 #include <cstdlib>
 #include <vector>
@@ -154,7 +155,8 @@ __global__ __launch_bounds__(256) void row_gather_one_kernel(int64_t n, const in
     }
 }
 
-// W[g] = sum of the squared lengths of CSR row g, in the same order
+// W[g] = sum of the squared lengths of CSR row g: lane e the entries e + 64 i by
+// ascending i, the lanes by a butterfly
 template <typename LenT>
 __global__ __launch_bounds__(256) void row_squares_kernel(int64_t n, const int64_t* __restrict__ rp,
                                                           const LenT* __restrict__ ln, double* __restrict__ W)

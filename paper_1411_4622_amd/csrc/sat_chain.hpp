@@ -1828,8 +1828,6 @@ __device__ void run_chain_piped(const ChainJob& J, char* lds, ChainShared& sh, b
         return v;
     };
 
-    // the value of a ray in the LDS part (for any other, some word of LDS)
-    auto lget = [&](int tk) -> Real { return in_lds(tk) ? rl[tk & ~kLdsFlag] : pval[0]; };
     // the values of a set that is scored next, before the loop or after a resync
     auto first_value = [&](RowSet<Real, E>& S, int e) {
         if (in_lds(S.tk[e]))
