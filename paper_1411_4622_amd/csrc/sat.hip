@@ -142,8 +142,9 @@ bool ahead_allowed(const sat_params* p)
 {
     // redrawn proposals depend on the image value at the step, and blocks of
     // 16 to 64 steps are numbered in 32 bits (a chain of more than 2^34 steps
-    // would run for hours on end before it got there)
-    return p->proposal == PILA_PROP_CLAMP && p->n_steps <= (int64_t)1 << 34;
+    // would run for hours on end before it got there), and stages in few enough
+    // bits to add two remainders (ShortSchedule)
+    return p->proposal == PILA_PROP_CLAMP && p->n_steps <= (int64_t)1 << 34 && p->n_stages <= kShortStages;
 }
 
 bool piped_allowed(const pila_geom* g, const pila_csr* c)
@@ -641,7 +642,7 @@ constexpr size_t kSplitWordBytes = 2 * kMaxCand * 2 * sizeof(unsigned long long)
 
 bool split_wanted(const pila_csr* c, const sat_params* p)
 {
-    return p->m_cand >= kSplitMinM && c->n_support > 0 &&
+    return p->m_cand >= kSplitMinM && c->n_support > 0 && p->n_stages <= kShortStages &&
            (int64_t)p->m_cand * (c->nnz / c->n_support) >= kSplitMinEntries;
 }
 

@@ -18,7 +18,7 @@ ChainJob make_job(const pila_geom* g, const pila_csr* c, const double* sino, con
                   double* image, char* ws);
 int device_props(hipDeviceProp_t* prop);
 // whether the pipelined and long-row bodies, which draw a block of steps ahead,
-// can take a chain (the general and split bodies take any)
+// can take a chain (the general body takes any)
 bool ahead_allowed(const sat_params* p);
 // whether the pipelined body's index arithmetic holds for this PILA
 bool piped_allowed(const pila_geom* g, const pila_csr* c);
