@@ -23,7 +23,7 @@
 // function, so they hold bit-identical lengths.
 //
 // 1024 x 1024, 720 angles, FP32, circular support (7.6e8 entries, 12 GB
-// written; 1.8 ms at the rate of a fill): 6.5 ms, of it counts 1.4, pixel fill
+// written; 1.8 ms at the rate of a fill): 6.3 ms, of it counts 1.4, pixel fill
 // 2.45, ray fill 2.4 ms.  Counting and filling by evaluating the full chord at
 // four candidate bins per (pixel, angle), the rays by a lane per image row,
 // and one-workgroup scans took 31.9 ms (4.1 + 6.2, 6.1, 11.5, 1.9 ms);
